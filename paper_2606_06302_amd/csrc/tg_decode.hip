@@ -137,6 +137,7 @@ struct DecodeParams {
   float scale_log2;          // sm_scale * log2(e)
   float scale;               // sm_scale
   int32_t* merge_counters;   // [B*H] arrival counters of the in-launch merge, or NULL
+  int32_t merge_lanes;       // chains a unit's partials are merged in (merge_lanes() below)
   // in-launch decode-token append (open items only), or append_k == NULL
   const u4* append_k;        // [B][H] token rows, 16-byte chunks
   const u4* append_v;
@@ -801,47 +802,67 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
         const int s = unit_splits[u], base = unit_base[u];
         if (__builtin_amdgcn_readfirstlane(arrived[j]) != s - 1) continue;
         if (col < G) {
-          float mr = -INFINITY, L = 0.f;
+          // the same chains (piece i in chain i mod merge_lanes), the same
+          // recurrence and the same order as the merge kernels
+          const int lanes = p.merge_lanes;
+          float M = -INFINITY;   // the largest lse, which the chains are combined at
+          if (lanes > 1)
+            for (int i = 0; i < s; ++i)
+              M = fmaxf(M, __hip_atomic_load(p.part_lse + ((int64_t)base + i) * G + col, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT));
+          float L = 0.f;
           f32x4 A[8];
 #pragma unroll
           for (int mm = 0; mm < 8; ++mm) A[mm] = f32x4{0.f, 0.f, 0.f, 0.f};
-          // up to kSplitBatch partials are requested before the first is
-          // used: one round trip for a unit of that many splits (indices past
-          // the last re-read it, and selects discard their steps)
-          constexpr int kSplitBatch = 4;
-          for (int i0 = 0; i0 < s; i0 += kSplitBatch) {
-            float lv[kSplitBatch];
-            f32x4 ov[kSplitBatch][8];
+          for (int w = 0; w < min(lanes, s); ++w) {
+            float mr = -INFINITY, Lc = 0.f;
+            f32x4 Ac[8];
 #pragma unroll
-            for (int jj = 0; jj < kSplitBatch; ++jj) {
-              const int64_t pidx = (int64_t)base + min(i0 + jj, s - 1);
-              lv[jj] = __hip_atomic_load(p.part_lse + pidx * G + col, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              const uint64_t* prow = reinterpret_cast<const uint64_t*>(p.part_o + (pidx * G + col) * D + 4 * rb);
+            for (int mm = 0; mm < 8; ++mm) Ac[mm] = f32x4{0.f, 0.f, 0.f, 0.f};
+            // up to kSplitBatch partials are requested before the first is
+            // used: one round trip for a chain of that many splits (indices
+            // past the last re-read it, and selects discard their steps)
+            constexpr int kSplitBatch = 4;
+            for (int i0 = w; i0 < s; i0 += kSplitBatch * lanes) {
+              float lv[kSplitBatch];
+              f32x4 ov[kSplitBatch][8];
 #pragma unroll
-              for (int mm = 0; mm < 8; ++mm) {
-                const uint64_t lo = __hip_atomic_load(prow + mm * 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const uint64_t hi = __hip_atomic_load(prow + mm * 8 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ov[jj][mm] = f32x4{__uint_as_float((uint32_t)lo), __uint_as_float((uint32_t)(lo >> 32)),
-                                   __uint_as_float((uint32_t)hi), __uint_as_float((uint32_t)(hi >> 32))};
+              for (int jj = 0; jj < kSplitBatch; ++jj) {
+                const int64_t pidx = (int64_t)base + min(i0 + jj * lanes, s - 1);
+                lv[jj] = __hip_atomic_load(p.part_lse + pidx * G + col, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint64_t* prow = reinterpret_cast<const uint64_t*>(p.part_o + (pidx * G + col) * D + 4 * rb);
+#pragma unroll
+                for (int mm = 0; mm < 8; ++mm) {
+                  const uint64_t lo = __hip_atomic_load(prow + mm * 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                  const uint64_t hi = __hip_atomic_load(prow + mm * 8 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                  ov[jj][mm] = f32x4{__uint_as_float((uint32_t)lo), __uint_as_float((uint32_t)(lo >> 32)),
+                                     __uint_as_float((uint32_t)hi), __uint_as_float((uint32_t)(hi >> 32))};
+                }
+              }
+#pragma unroll
+              for (int jj = 0; jj < kSplitBatch; ++jj) {
+                const bool use = i0 + jj * lanes < s;
+                const float mn = fmaxf(mr, lv[jj]);
+                const float a = __expf(mr - mn), wt = __expf(lv[jj] - mn);
+                const float Ln = fmaf(Lc, a, wt);
+#pragma unroll
+                for (int mm = 0; mm < 8; ++mm)
+#pragma unroll
+                  for (int q = 0; q < 4; ++q) {
+                    const float An = fmaf(Ac[mm][q], a, wt * ov[jj][mm][q]);
+                    Ac[mm][q] = use ? An : Ac[mm][q];
+                  }
+                Lc = use ? Ln : Lc;
+                mr = use ? mn : mr;
               }
             }
-            // the same running-max recurrence, in the same order, as tg_merge_kernel
+            if (lanes == 1) M = mr;
+            const float f = lanes == 1 ? 1.f : __expf(mr - M);
+            L = fmaf(Lc, f, L);
 #pragma unroll
-            for (int jj = 0; jj < kSplitBatch; ++jj) {
-              const bool use = i0 + jj < s;
-              const float mn = fmaxf(mr, lv[jj]);
-              const float a = __expf(mr - mn), w = __expf(lv[jj] - mn);
-              const float Ln = fmaf(L, a, w);
+            for (int mm = 0; mm < 8; ++mm)
 #pragma unroll
-              for (int mm = 0; mm < 8; ++mm)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                  const float An = fmaf(A[mm][q], a, w * ov[jj][mm][q]);
-                  A[mm][q] = use ? An : A[mm][q];
-                }
-              L = use ? Ln : L;
-              mr = use ? mn : mr;
-            }
+              for (int q = 0; q < 4; ++q) A[mm][q] = fmaf(Ac[mm][q], f, A[mm][q]);
           }
           const int qh = h * G + col;
           uint2* orow =
@@ -851,7 +872,7 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
             orow[mm * 4] =
                 make_uint2(uint32_t(f32_to_bf16(A[mm][0] / L)) | (uint32_t(f32_to_bf16(A[mm][1] / L)) << 16),
                            uint32_t(f32_to_bf16(A[mm][2] / L)) | (uint32_t(f32_to_bf16(A[mm][3] / L)) << 16));
-          if (p.lse && rb == 0) p.lse[(int64_t)b * p.num_q_heads + qh] = mr + logf(L);
+          if (p.lse && rb == 0) p.lse[(int64_t)b * p.num_q_heads + qh] = M + logf(L);
         }
         if (lane == 0) __hip_atomic_store(p.merge_counters + u, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
@@ -924,14 +945,106 @@ __global__ void __launch_bounds__(kBlock) tg_merge_kernel(const int32_t* __restr
   if (lse && e == 0) lse[row0 + g] = m + logf(L);
 }
 
+// The same merge for units cut into many pieces: W chains per unit and head,
+// chain w taking pieces w, w + W, ... with the recurrence above, then the
+// chains combined in order at the largest of their maxima.  One workgroup per
+// (unit, head): D/4 threads per chain, four outputs each.
+// What bounds the single chain is latency: it pays a memory round trip per
+// kBatch pieces, and one request's long context on 1024 workers leaves units
+// of hundreds of pieces on a handful of workgroups.  Measured (gqa 8, head_dim
+// 128, 8 units with 1027 pieces, at most 368 per unit): 44 us in one chain,
+// 14, 8.1, 5.6 and 5.8 us in 4, 8, 16 and 32.
+template <typename T, int D, int W>
+__global__ void __launch_bounds__(D / 4 * W) tg_merge_chains_kernel(
+    const int32_t* __restrict__ unit_splits, const int32_t* __restrict__ unit_base, const float* __restrict__ part_o,
+    const float* __restrict__ part_lse, void* out, float* lse, int32_t num_kv_heads, int32_t gqa) {
+  constexpr int kTpc = D / 4;   // threads per chain
+  __shared__ f32x4 sm_A[W][kTpc];
+  __shared__ float sm_m[W], sm_L[W];
+  const int u = blockIdx.x, g = blockIdx.y;
+  const int s = unit_splits[u];
+  const int base = unit_base[u];
+  asm volatile("" ::"s"(s), "s"(base));   // both reads in flight before the exit test
+  if (s <= 1) return;
+  const int t = threadIdx.x % kTpc, w = threadIdx.x / kTpc;
+  const float* pl = part_lse + (int64_t)base * gqa + g;
+  const f32x4* po = reinterpret_cast<const f32x4*>(part_o + ((int64_t)base * gqa + g) * D) + t;
+  float m = -INFINITY, L = 0.f;
+  f32x4 A = {0.f, 0.f, 0.f, 0.f};
+  constexpr int kBatch = 4;
+  for (int i0 = w; i0 < s; i0 += kBatch * W) {
+    float lv[kBatch];
+    f32x4 ov[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int64_t i = min(i0 + j * W, s - 1);
+      lv[j] = pl[i * gqa];
+      ov[j] = po[i * gqa * kTpc];
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const bool use = i0 + j * W < s;
+      const float mn = fmaxf(m, lv[j]);
+      const float a = __expf(m - mn), wt = __expf(lv[j] - mn);
+      const float Ln = fmaf(L, a, wt);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float An = fmaf(A[q], a, wt * ov[j][q]);
+        A[q] = use ? An : A[q];
+      }
+      L = use ? Ln : L;
+      m = use ? mn : m;
+    }
+  }
+  sm_A[w][t] = A;
+  if (t == 0) {
+    sm_m[w] = m;
+    sm_L[w] = L;
+  }
+  __syncthreads();
+  if (w > 0) return;
+  const int n = min(W, s);   // chains that hold a piece
+  float M = -INFINITY;
+  for (int c = 0; c < n; ++c) M = fmaxf(M, sm_m[c]);
+  L = 0.f;
+  A = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < n; ++c) {
+    const float f = __expf(sm_m[c] - M);
+    const f32x4 Ac = sm_A[c][t];
+    L = fmaf(sm_L[c], f, L);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) A[q] = fmaf(Ac[q], f, A[q]);
+  }
+  const int b = u / num_kv_heads, h = u % num_kv_heads;
+  const int64_t row = (int64_t)b * num_kv_heads * gqa + (int64_t)h * gqa + g;
+  store_out4<T>(static_cast<T*>(out) + row * D + 4 * t, A[0] / L, A[1] / L, A[2] / L, A[3] / L);
+  if (lse && t == 0) lse[row] = M + logf(L);
+}
+
 using MergeFn = void (*)(const int32_t*, const int32_t*, const float*, const float*, void*, float*, int32_t,
                          int32_t);
 
-MergeFn pick_merge(int dtype, int d) {
-  if (dtype == TG_F32 && d == 64) return &tg_merge_kernel<float, 64>;
-  if (dtype == TG_F32 && d == 128) return &tg_merge_kernel<float, 128>;
-  if (dtype == TG_BF16 && d == 64) return &tg_merge_kernel<uint16_t, 64>;
-  if (dtype == TG_BF16 && d == 128) return &tg_merge_kernel<uint16_t, 128>;
+// Chains a unit's partials are merged in, by the plan's pieces per unit (the
+// lengths are ragged: the longest units hold about three times the mean).
+// Measured, one chain against 16 (gqa 4 unless said): 6.3 pieces per unit (192
+// units) 4.8 against 4.7 us, 6.9 (128 units, f32) 6.9 against 4.8, 17 (64
+// units) 7.4 against 4.6, 33 (32 units, gqa 8) 13.2 against 3.9; with 5 per
+// unit (256 units, gqa 8) the 16 chains' workgroups cost more than the round
+// trips they save, 6.0 against 4.7.  8 chains are level with 16 up to 17
+// pieces and behind above; 32 are never ahead by more than 0.7 us.
+constexpr int kMergeLanes = 16;
+int merge_lanes(int64_t num_partials, int64_t units) { return num_partials < 6 * units ? 1 : kMergeLanes; }
+
+template <typename T, int D>
+MergeFn pick_merge_lanes(int lanes) {
+  return lanes == 1 ? &tg_merge_kernel<T, D> : &tg_merge_chains_kernel<T, D, kMergeLanes>;
+}
+
+MergeFn pick_merge(int dtype, int d, int lanes) {
+  if (dtype == TG_F32 && d == 64) return pick_merge_lanes<float, 64>(lanes);
+  if (dtype == TG_F32 && d == 128) return pick_merge_lanes<float, 128>(lanes);
+  if (dtype == TG_BF16 && d == 64) return pick_merge_lanes<uint16_t, 64>(lanes);
+  if (dtype == TG_BF16 && d == 128) return pick_merge_lanes<uint16_t, 128>(lanes);
   return nullptr;
 }
 
@@ -1065,6 +1178,7 @@ int32_t decode_impl(const tg_decode_args* a, void* ws_ptr, size_t ws_bytes, void
   // caller passes arrival counters; every other case merges in a second launch
   const bool fused_merge = a->merge_counters && a->num_partials > 0 && a->dtype == TG_BF16 && g.head_dim == 128;
   p.merge_counters = fused_merge ? a->merge_counters : nullptr;
+  p.merge_lanes = merge_lanes(a->num_partials, (int64_t)a->batch * g.num_kv_heads);
   p.scale = a->sm_scale != 0.f ? a->sm_scale : 1.0f / std::sqrt((float)g.head_dim);
   p.scale_log2 = p.scale * kLog2e;
   if (a->num_items == 0) return TG_OK;
@@ -1076,9 +1190,11 @@ int32_t decode_impl(const tg_decode_args* a, void* ws_ptr, size_t ws_bytes, void
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "decode launch failed: %s", hipGetErrorString(e));
   if (a->num_partials > 0 && !fused_merge) {
-    MergeFn mf = pick_merge(a->dtype, g.head_dim);
-    hipLaunchKernelGGL(mf, dim3(a->batch * g.num_kv_heads, (gqa * g.head_dim / 4 + kBlock - 1) / kBlock), dim3(kBlock), 0,
-                       st, a->unit_splits,
+    MergeFn mf = pick_merge(a->dtype, g.head_dim, p.merge_lanes);
+    // one chain: four outputs per thread; several: a workgroup per (unit, head), D/4 threads per chain
+    const int block = p.merge_lanes == 1 ? kBlock : g.head_dim / 4 * p.merge_lanes;
+    const int grid_y = p.merge_lanes == 1 ? (gqa * g.head_dim / 4 + kBlock - 1) / kBlock : gqa;
+    hipLaunchKernelGGL(mf, dim3(a->batch * g.num_kv_heads, grid_y), dim3(block), 0, st, a->unit_splits,
                        a->unit_partial_base, p.part_o, p.part_lse, a->out, a->lse, g.num_kv_heads, gqa);
     e = hipGetLastError();
     if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "merge launch failed: %s", hipGetErrorString(e));

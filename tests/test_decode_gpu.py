@@ -325,6 +325,32 @@ def test_fused_merge_matches_two_launch_merge_bitwise(gqa, mode, n_bins, st):
         compare_layer(fused, l, what=f"fused merge layer {l}")
 
 
+@pytest.mark.parametrize("dtype,d,gqa", [("bf16", 128, 8), ("bf16", 64, 3), ("f32", 128, 1), ("f32", 64, 5)])
+@pytest.mark.parametrize("pieces", [10, 11, 15, 16, 17, 63, 64, 65, 190])
+def test_merge_chain_edges(dtype, d, gqa, pieces):
+    """Piece counts on both sides of the merge's switch to several chains (6 per unit on average: 10 and 11
+    pieces here), of the chain count (16) and of a chain's load batch (4 pieces), with one short unit cut into
+    fewer pieces and one not cut at all, against the oracle; where the in-launch merge exists, it gives the same bits."""
+    _gpu()
+    g = Geometry(1, 4, 4 * gqa, d, 16, 2)
+    budget = np.array([[1.0, 0.9, 0.011, 1e-4]])   # pages: 200, 180, 3 and 1
+    wl = custom(8100 + pieces, g, 1, dtype, 3200, budget=budget, jitter=0.0, kv_scale=0.5)
+    tables = Tables(wl)
+    pool = torch.from_numpy(poisoned_host_pool(wl, tables)).to({"f32": torch.float32,
+                                                                "bf16": torch.bfloat16}[dtype]).cuda()
+    kw = dict(tables=tables, mode=tg.TG_PLAN_UNIFORM, n_bins=4 * pieces, fill="host", pool=pool)
+    s = DecodeSession(wl, **kw)
+    assert s.plans[0]["unit_splits"].max() == min(pieces, 200) and s.plans[0]["unit_splits"].min() == 1
+    s.run_step()
+    torch.cuda.synchronize()
+    compare_layer(s, 0, what=f"{dtype} d{d} pieces {pieces}")
+    if dtype == "bf16" and d == 128:
+        f = DecodeSession(wl, fused_merge=True, q=s.q, **kw)
+        f.run_step()
+        torch.cuda.synchronize()
+        assert torch.equal(f.out, s.out) and torch.equal(f.lse, s.lse)
+
+
 def test_read_probe_checksums():
     """The streaming-read probe reads exactly the slabs the decode reads: every worker's XOR checksum equals
     the host's over the same (page, slot) K and V slabs."""
