@@ -395,8 +395,17 @@ int32_t tg_append(const tg_append_args* args, void* hip_stream);
  * TG_PREFILL_TILE keys.  The result does not depend on block_order.
  * A history length outside [0, pages of the head's table * page_size] is
  * clamped to that range on the device.
+ * workspace: NULL, or tg_prefill_workspace_bytes(args) bytes (no
+ *   initialisation needed; calls that share one must not overlap in time) for
+ *   the key-split launch: blocks much longer than the others are cut by keys,
+ *   their fp32 partials merged by a second launch on the same stream, and
+ *   block_order is not used.  It pays where the longest block, in tiles, is
+ *   longer than about 1.25 times the launch's tiles / 208, plus 12: few
+ *   requests, or very unequal histories.  The size is 0, and a workspace is
+ *   not used, past 512 (request, KV head) units or 1024 blocks; one that is
+ *   too small or not 16-byte aligned is not used either.
  * Supported: dtype TG_BF16, head_dim 64 or 128, page_size 16, gqa 1..16,
- * chunk_len >= 1.  The kernel needs no workspace (workspace may be NULL). */
+ * chunk_len >= 1. */
 typedef struct {
   tg_geometry geom;
   int32_t batch;

@@ -15,7 +15,9 @@
 // to the workgroup's last row.  Blocks are placed XCD-aware: all row tiles of
 // a (b, h) run on the same XCD (block id mod 8), so the history they share is
 // read into one L2; the host schedule (tg_prefill_schedule) balances the units
-// over the XCDs by their tile counts and starts the longest blocks first.
+// over the XCDs by their tile counts and starts the longest blocks first.  Given
+// a workspace, blocks much longer than the rest are cut by keys (key-split
+// launch, below).
 //
 // Data movement.  Tiles stream into a 4-deep LDS ring with gfx950's
 // global_load_lds_dwordx4 (no staging registers); wave w fetches key rows
@@ -58,6 +60,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4_vs __attribute__((__vector_size__(4 * sizeof(__bf16))));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 
 #define TG_CONST __attribute__((address_space(4)))
@@ -111,7 +114,44 @@ struct PrefillParams {
   int32_t batch, chunk, layer, num_layers, num_kv_heads, num_groups, heads_per_group, gqa;
   int32_t row_tiles;        // ceil(chunk*gqa / kRows)
   float scale_log2;
+  // key-split launch only
+  f32x4* part_o;            // [kSplitSlots][part_waves][D/4][32 rows] unnormalised fp32 outputs
+  float* part_ml;           // [kSplitSlots][part_waves][2][32 rows]: reference maximum, sum
+  int2* pieces;             // [units * row_tiles]: first partial slot and piece count of every block
+  int32_t part_waves;       // waves of a block that own rows: min(8, ceil(chunk*gqa / 32))
+  int32_t last_tiles;       // key tiles of the chunk that a unit's last row tile sees
 };
+
+// Key-split launch.  The longest block bounds a launch of few or very unequal
+// blocks: one request of 8 KV heads, chunk 512, is 64 blocks on 256 CUs, and
+// the two long heads' 16 blocks hold 65 % of the key tiles.  With a workspace,
+// blocks of more than T key tiles are cut into equal pieces of at most T, one
+// workgroup each, which leave fp32 partials (accumulator, reference maximum,
+// sum) for a second launch to merge.  T = max(kSplitMinTiles, total / target),
+// so there are at most `target` pieces more than blocks.  Every workgroup
+// derives the cut from the lengths itself: one thread per unit, the cut units
+// first, then the others in seven classes of descending length, so that the
+// longest pieces start first.  The row tiles of one (unit, piece) share its keys and run side
+// by side on one XCD (workgroup id mod 8), the (unit, piece) groups
+// round-robin over the XCDs.
+//
+// Measured, whole blocks against cut ones: one request, head_dim 128, chunk
+// 512 over a 16384-token history 440 -> 76 us, chunk 16 over 8192 153 -> 20
+// us; four requests, chunk 512 over 8192 166 -> 117 us; head_dim 64, five
+// requests, chunk 333, 74 -> 50 us.  Where no block is much longer than the
+// mean per CU the merge costs more than the cut saves (four requests, chunk
+// 512 over 2048 tokens: 61 against 72 us): the caller gives no workspace there.
+constexpr int kSplitMinTiles = 3;
+constexpr int kSplitMaxUnits = kBlock;   // one thread per unit
+constexpr int kSplitMaxBlocks = 1024;    // past it blocks outnumber the CUs by far and even out by themselves
+// Pieces to aim at: a little under the workgroups that run at once (one per CU
+// at head_dim 128, two at 64), because cutting into equal pieces rounds up.
+// One request, chunk 512, 16384 tokens, with 160 / 208 / 256 / 320: 94 / 81 /
+// 110 / 99 us at 128; two requests with 208 / 352 / 448 / 512: 84 / 78 / 70 /
+// 86 us at 64.
+constexpr int split_target(int d) { return d == 128 ? 208 : 448; }
+// a cut unit of n tiles has at most n / T + 1 <= 2n / T pieces
+constexpr int split_slots(int d) { return 2 * split_target(d); }
 
 __device__ __forceinline__ f32x16 mfma(const u4& a, const u4& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
@@ -146,21 +186,103 @@ __device__ __forceinline__ u2v lds_read_tr16(const void* ptr) {
   return __builtin_bit_cast(u2v, __builtin_amdgcn_ds_read_tr16_b64_v4bf16((TG_LDS bf16x4_vs*)ptr));
 }
 
-template <int D>
-__global__ void __launch_bounds__(kBlock) tg_prefill_kernel(PrefillParams p) {
+// Inclusive sum over the lanes of a wave.
+__device__ __forceinline__ int wave_inclusive_sum(int x) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o);
+    if ((int)(threadIdx.x & 63) >= o) x += y;
+  }
+  return x;
+}
+
+template <int D, bool kSplit, int kWavesPerSimd>
+__global__ void __launch_bounds__(kBlock, kWavesPerSimd) tg_prefill_kernel(PrefillParams p) {
   using S = Shape<D>;
   constexpr int kChunks = S::kChunks, kDmaInst = S::kDmaInst, kDmaPerTile = S::kDmaPerTile;
   constexpr int kTileBytes = S::kTileBytes, kRowsPerDma = S::kRowsPerDma;
   __shared__ u4 ring[kRing][2][kTile * kChunks];   // [slot][K, V][key row * kChunks + chunk position]
+  // key-split launch: a sum and the group counts per (class, wave), this workgroup's piece
+  __shared__ int64_t wave_sum[kSplit ? kWaves : 1];
+  __shared__ int32_t class_groups[kSplit ? 64 : 1];
+  __shared__ int32_t mine[kSplit ? 3 : 1];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_units = p.batch * p.num_kv_heads;
+  const int C = p.chunk, gqa = p.gqa;
+  const int Hq = p.num_kv_heads * gqa;
+  const int rows_total = C * gqa;
+
+  const TG_CONST int32_t* kv_len = (const TG_CONST int32_t*)p.kv_len;
+  const TG_CONST int32_t* group_of = (const TG_CONST int32_t*)p.group_of;
+  const TG_CONST int32_t* slot_of = (const TG_CONST int32_t*)p.slot_of;
+  const TG_CONST int64_t* pt_offsets = (const TG_CONST int64_t*)p.pt_offsets;
+  const TG_CONST int32_t* pt_pages = (const TG_CONST int32_t*)p.pt_pages;
 
   // block -> (unit, row tile): the host schedule, or units round-robin over
-  // the 8 XCDs (all row tiles of a unit on one XCD either way)
-  const int n_units = p.batch * p.num_kv_heads;
+  // the 8 XCDs (all row tiles of a unit on one XCD either way); in the
+  // key-split launch, the blocks of this worker's run
   int unit, rt;
-  if (p.block_order) {
+  int piece = 0, first_slot = 0, piece_tiles = 0;   // key-split launch
+  if constexpr (kSplit) {
+    const int u = threadIdx.x;
+    int n = 0;
+    if (u < n_units) {
+      const int ub = u / p.num_kv_heads, uh = u % p.num_kv_heads;
+      const int64_t ti = ((int64_t)ub * p.num_layers + p.layer) * p.num_groups +
+                         p.group_of[(int64_t)p.layer * p.num_kv_heads + uh];
+      const int64_t ucap = (p.pt_offsets[ti + 1] - p.pt_offsets[ti]) * kPage;
+      const int64_t len = p.kv_len[((int64_t)ub * p.num_layers + p.layer) * p.num_kv_heads + uh];
+      n = (int)((max<int64_t>(0, min<int64_t>(len, ucap)) + kTile - 1) / kTile) + p.last_tiles;
+    }
+    int64_t sum = n;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor((long long)sum, o);
+    if (lane == 0) wave_sum[wave] = sum;
+    if (threadIdx.x == 0) mine[0] = -1;
+    __syncthreads();
+    sum = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) sum += wave_sum[w];
+    constexpr int kTarget = split_target(D);
+    const int64_t total = sum * p.row_tiles;
+    piece_tiles = (int)max<int64_t>(kSplitMinTiles, (total + kTarget - 1) / kTarget);
+    const int np = (n + piece_tiles - 1) / piece_tiles;   // 0 past the last unit
+    // the unit's place in the order: its class's first group, then units by
+    // index; class 0 is the cut units, 1..7 the others by descending length
+    const int cls = np > 1 ? 0 : 7 - (int)((int64_t)min(n, piece_tiles) * 6 / piece_tiles);
+    int before = 0;    // groups before this unit's within its class and wave
+    int count = 0;     // lane c: groups of class c in this wave
+#pragma unroll
+    for (int c = 1; c < 8; ++c) {
+      const uint64_t in = __ballot(np == 1 && cls == c);
+      if (cls == c) before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));
+      if (lane == c) count = __popcll(in);
+    }
+    const int cut = np > 1 ? np : 0;
+    const int cut_sum = wave_inclusive_sum(cut);
+    if (cls == 0) before = cut_sum - cut;
+    const int cut_all = __shfl(cut_sum, 63);
+    if (lane == 0) count = cut_all;
+    if (lane < 8) class_groups[8 * lane + wave] = count;
+    __syncthreads();
+    const int in_order = class_groups[lane];   // (class, wave) in order
+    before += __shfl(wave_inclusive_sum(in_order) - in_order, 8 * cls + wave);
+    const int g = ((int)blockIdx.x >> 3) / p.row_tiles * 8 + (blockIdx.x & 7);   // (unit, piece) group
+    rt = ((int)blockIdx.x >> 3) % p.row_tiles;
+    if (before <= g && g < before + np) {   // exactly one unit, or none past the last group
+      mine[0] = u;
+      mine[1] = g - before;
+      mine[2] = before;   // the cut units come first: their groups are the partial slots
+    }
+    __syncthreads();
+    unit = __builtin_amdgcn_readfirstlane(mine[0]);
+    piece = __builtin_amdgcn_readfirstlane(mine[1]);
+    first_slot = __builtin_amdgcn_readfirstlane(mine[2]);
+    piece_tiles = __builtin_amdgcn_readfirstlane(piece_tiles);
+    if (unit < 0) return;
+  } else if (p.block_order) {
     const int code = ((const TG_CONST int32_t*)p.block_order)[blockIdx.x];
     if (code < 0 || code >= n_units * p.row_tiles) return;
     unit = code / p.row_tiles;
@@ -171,18 +293,8 @@ __global__ void __launch_bounds__(kBlock) tg_prefill_kernel(PrefillParams p) {
     rt = local % p.row_tiles;
     if (unit >= n_units) return;
   }
+
   const int b = unit / p.num_kv_heads, h = unit % p.num_kv_heads;
-  const int C = p.chunk, gqa = p.gqa;
-  const int Hq = p.num_kv_heads * gqa;
-  const int rows_total = C * gqa;
-  const int row0 = rt * kRows;
-
-  const TG_CONST int32_t* kv_len = (const TG_CONST int32_t*)p.kv_len;
-  const TG_CONST int32_t* group_of = (const TG_CONST int32_t*)p.group_of;
-  const TG_CONST int32_t* slot_of = (const TG_CONST int32_t*)p.slot_of;
-  const TG_CONST int64_t* pt_offsets = (const TG_CONST int64_t*)p.pt_offsets;
-  const TG_CONST int32_t* pt_pages = (const TG_CONST int32_t*)p.pt_pages;
-
   const int grp = group_of[(int64_t)p.layer * p.num_kv_heads + h];
   const int slot = slot_of[(int64_t)p.layer * p.num_kv_heads + h];
   const int64_t tidx = ((int64_t)b * p.num_layers + p.layer) * p.num_groups + grp;
@@ -191,34 +303,20 @@ __global__ void __launch_bounds__(kBlock) tg_prefill_kernel(PrefillParams p) {
   const int64_t cap = (pt_offsets[tidx + 1] - tbase) * kPage;
   const int hist = (int)max<int64_t>(0, min<int64_t>(kv_len[((int64_t)b * p.num_layers + p.layer) * p.num_kv_heads + h], cap));
   const int npages = (hist + kPage - 1) / kPage;
-  const int i_last = min(C - 1, (min(row0 + kRows, rows_total) - 1) / gqa);   // last chunk row of the block
   const int n_hist_tiles = (hist + kTile - 1) / kTile;
+  const int row0 = rt * kRows;
+  const int i_last = min(C - 1, (min(row0 + kRows, rows_total) - 1) / gqa);   // last chunk row of the block
   const int n_tiles = n_hist_tiles + (i_last + kTile) / kTile;
-
-  // this lane's two query rows (one per column block)
-  const int hf = lane >> 5;
-  int my_i[kCB];
-  bool row_ok[kCB];
-  u4 qb[kCB][S::kK];
-#pragma unroll
-  for (int cb = 0; cb < kCB; ++cb) {
-    const int r = row0 + wave * kRowsPerWave + cb * 32 + (lane & 31);
-    row_ok[cb] = r < rows_total;
-    my_i[cb] = row_ok[cb] ? r / gqa : 0;
-    const int j = row_ok[cb] ? r % gqa : 0;
-    const u4* qp = reinterpret_cast<const u4*>(p.q + (((int64_t)b * C + my_i[cb]) * Hq + h * gqa + j) * D);
-#pragma unroll
-    for (int kk = 0; kk < S::kK; ++kk) qb[cb][kk] = row_ok[cb] ? qp[kk * 2 + hf] : u4(0u);
+  int t_begin = 0, t_end = n_tiles, np = 1;
+  if constexpr (kSplit) {
+    np = (n_tiles + piece_tiles - 1) / piece_tiles;   // fewer than the unit's where the row tile sees less of the chunk
+    if (piece == 0 && threadIdx.x == 0) p.pieces[unit * p.row_tiles + rt] = make_int2(first_slot * p.row_tiles + rt, np);
+    if (piece >= np) return;
+    t_begin = (int)((int64_t)piece * n_tiles / np);
+    t_end = (int)((int64_t)(piece + 1) * n_tiles / np);
   }
-  // Settle the query loads here, once: the compiler's wait-count pass cannot
-  // see the inline-assembly LDS DMAs, so a load still pending at the loop
-  // entry would make it wait for vmcnt(0) - every DMA in flight - at the first
-  // use of qb on every tile.  Routing qb through an empty asm places that one
-  // wait before the loop and leaves no compiler-tracked load behind.
-#pragma unroll
-  for (int cb = 0; cb < kCB; ++cb)
-#pragma unroll
-    for (int kk = 0; kk < S::kK; ++kk) asm volatile("" : "+v"(qb[cb][kk]));
+
+  const int hf = lane >> 5;
   const int wave_i_max = min(C - 1, (min(row0 + wave * kRowsPerWave + kRowsPerWave, rows_total) - 1) / gqa);
   const int wave_i_min = min(C - 1, (row0 + wave * kRowsPerWave) / gqa);
 
@@ -275,14 +373,38 @@ __global__ void __launch_bounds__(kBlock) tg_prefill_kernel(PrefillParams p) {
   const int tr_dim = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);   // dims within a 32-dim block
   const int tr_chunk = tr_dim >> 3, tr_half = (tr_dim >> 2) & 1;
 
-  // prologue: tiles 0 .. kRing-2 in flight
+  // this lane's query row
+  int my_i[kCB];
+  bool row_ok[kCB];
+  u4 qb[kCB][S::kK];
+#pragma unroll
+  for (int cb = 0; cb < kCB; ++cb) {
+    const int r = row0 + wave * kRowsPerWave + cb * 32 + (lane & 31);
+    row_ok[cb] = r < rows_total;
+    my_i[cb] = row_ok[cb] ? r / gqa : 0;
+    const int j = row_ok[cb] ? r % gqa : 0;
+    const u4* qp = reinterpret_cast<const u4*>(p.q + (((int64_t)b * C + my_i[cb]) * Hq + h * gqa + j) * D);
+#pragma unroll
+    for (int kk = 0; kk < S::kK; ++kk) qb[cb][kk] = row_ok[cb] ? qp[kk * 2 + hf] : u4(0u);
+  }
+  // Settle the query loads here, once: the compiler's wait-count pass cannot
+  // see the inline-assembly LDS DMAs, so a load still pending at the loop
+  // entry would make it wait for vmcnt(0) - every DMA in flight - at the first
+  // use of qb on every tile.  Routing qb through an empty asm places that one
+  // wait before the loop and leaves no compiler-tracked load behind.
+#pragma unroll
+  for (int cb = 0; cb < kCB; ++cb)
+#pragma unroll
+    for (int kk = 0; kk < S::kK; ++kk) asm volatile("" : "+v"(qb[cb][kk]));
+  // prologue: the first kRing-1 tiles in flight (ring slot = tile - t_begin
+  // modulo kRing)
 #pragma unroll
   for (int r = 0; r < kRing - 1; ++r)
-    if (r < n_tiles) issue(r, r);
+    if (t_begin + r < t_end) issue(t_begin + r, r);
 
-  for (int t = 0; t < n_tiles; ++t) {
+  for (int t = t_begin; t < t_end; ++t) {
     // tile t has landed once at most the DMAs of the tiles after it are pending
-    const int after = min(kRing - 2, n_tiles - 1 - t);
+    const int after = min(kRing - 2, t_end - 1 - t);
     if (after >= 2)
       wait_vmcnt<2 * kDmaPerTile>();
     else if (after == 1)
@@ -292,16 +414,16 @@ __global__ void __launch_bounds__(kBlock) tg_prefill_kernel(PrefillParams p) {
     if (t < n_hist_tiles && t * kTile + wave * kDmaRows + kDmaRows > hist) {
       // this wave's share holds V rows past the retained history: they may
       // hold anything (NaN included) and p = 0 does not cancel NaN, so zero them
-      u4* vq = &ring[t % kRing][1][wave * kDmaRows * kChunks];
+      u4* vq = &ring[(t - t_begin) % kRing][1][wave * kDmaRows * kChunks];
 #pragma unroll
       for (int j = 0; j < kDmaInst; ++j)
         if (t * kTile + wave * kDmaRows + j * kRowsPerDma + rl >= hist) vq[j * 64 + lane] = u4(0u);
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
     barrier();   // tile t complete in LDS; every wave is done with tile t-1
-    if (t + kRing - 1 < n_tiles) issue(t + kRing - 1, (t + kRing - 1) % kRing);
+    if (t + kRing - 1 < t_end) issue(t + kRing - 1, (t - t_begin + kRing - 1) % kRing);
 
-    const int s = t % kRing;
+    const int s = (t - t_begin) % kRing;
     const unsigned char* kt = reinterpret_cast<const unsigned char*>(&ring[s][0][0]);
     const unsigned char* vt = reinterpret_cast<const unsigned char*>(&ring[s][1][0]);
     const bool is_chunk = t >= n_hist_tiles;
@@ -373,7 +495,9 @@ __global__ void __launch_bounds__(kBlock) tg_prefill_kernel(PrefillParams p) {
 #pragma unroll
           for (int d = 0; d < S::kDB; ++d) acc[cb][d] *= alpha;
         }
-        const float mcs = m[cb] * cs;
+        // a piece may start with chunk keys that lie in the future of a row: its
+        // maximum is still -inf then, and its probabilities must be 0, not NaN
+        const float mcs = (kSplit && m[cb] == -INFINITY ? 0.f : m[cb]) * cs;
         uint32_t pw[8];
 #pragma unroll
         for (int r = 0; r < 16; r += 2) {
@@ -399,6 +523,23 @@ __global__ void __launch_bounds__(kBlock) tg_prefill_kernel(PrefillParams p) {
 #pragma unroll
   for (int cb = 0; cb < kCB; ++cb) {
     const float lt = swap32_sum(l[cb]);
+    if constexpr (kSplit) {
+      static_assert(kCB == 1, "one partial row per lane pair");
+      if (np > 1) {   // a piece: its partials, 16-byte stores contiguous over the 32 rows
+        if (wave < p.part_waves) {
+          const int64_t part = ((int64_t)(first_slot + piece) * p.row_tiles + rt) * p.part_waves + wave;
+          f32x4* po = p.part_o + part * (D / 4) * 32 + (lane & 31);
+#pragma unroll
+          for (int db = 0; db < S::kDB; ++db)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4)
+              po[(db * 8 + 2 * r4 + hf) * 32] = f32x4{acc[cb][db][r4 * 4 + 0], acc[cb][db][r4 * 4 + 1],
+                                                     acc[cb][db][r4 * 4 + 2], acc[cb][db][r4 * 4 + 3]};
+          p.part_ml[part * 64 + lane] = hf ? lt : m[cb];
+        }
+        continue;
+      }
+    }
     if (!row_ok[cb]) continue;
     const int r = row0 + wave * kRowsPerWave + cb * 32 + (lane & 31);
     const int i = r / gqa, j = r % gqa;
@@ -416,16 +557,91 @@ __global__ void __launch_bounds__(kBlock) tg_prefill_kernel(PrefillParams p) {
   }
 }
 
-}  // namespace
-
-extern "C" {
-
-size_t tg_prefill_workspace_bytes(const tg_prefill_args* args) {
-  (void)args;
-  return 0;
+// Merge of the key-split launch: the pieces of a block are combined at the
+// largest of their reference maxima (the pieces' sums and accumulators are
+// relative to them).  Grid (blocks, waves with rows x D/32): thread = (row,
+// four consecutive dims), so partial loads are contiguous over a wave's 32
+// rows.  Bound by reading the partials back: 9 us for 220 pieces of 256 rows
+// (29 MB).
+template <int D>
+__global__ void __launch_bounds__(256) tg_prefill_merge_kernel(PrefillParams p) {
+  const int2 k = p.pieces[blockIdx.x];
+  const int n = k.y;
+  if (n <= 1) return;
+  constexpr int kParts = D / 32;   // workgroups per 32 rows
+  const int unit = blockIdx.x / p.row_tiles, rt = blockIdx.x % p.row_tiles;
+  const int wave = blockIdx.y / kParts;
+  const int chunk = (threadIdx.x >> 5) + 8 * (blockIdx.y % kParts);
+  const int b = unit / p.num_kv_heads, h = unit % p.num_kv_heads;
+  const int row = threadIdx.x & 31;
+  const int r = rt * kRows + wave * kRowsPerWave + row;
+  if (r >= p.chunk * p.gqa) return;
+  auto part = [&](int i) { return ((int64_t)k.x + (int64_t)i * p.row_tiles) * p.part_waves + wave; };
+  constexpr int kBatch = 4;
+  float M = -INFINITY, L = 0.f;
+  f32x4 A = f32x4(0.f);
+  // kBatch pieces are requested before the first is used; past the last piece
+  // it is read again and not used
+  for (int i0 = 0; i0 < n; i0 += kBatch) {
+    float mv[kBatch], lv[kBatch];
+    f32x4 ov[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int64_t pt = part(min(i0 + j, n - 1));
+      mv[j] = p.part_ml[pt * 64 + row];
+      lv[j] = p.part_ml[pt * 64 + 32 + row];
+      ov[j] = p.part_o[(pt * (D / 4) + chunk) * 32 + row];
+    }
+    float Mn = M;
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) Mn = fmaxf(Mn, mv[j]);
+    // no visible key so far: nothing to rescale, and the weights below are 0
+    const float Mr = Mn == -INFINITY ? 0.f : Mn;
+    const float a = fast_exp2((M - Mr) * p.scale_log2);
+    L *= a;
+    A *= a;
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const bool use = i0 + j < n;
+      const float w = fast_exp2((mv[j] - Mr) * p.scale_log2);   // 0 for a piece with no visible key
+      L = use ? fmaf(lv[j], w, L) : L;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) A[q] = use ? fmaf(ov[j][q], w, A[q]) : A[q];
+    }
+    M = Mn;
+  }
+  const float inv = 1.f / L;
+  const int Hq = p.num_kv_heads * p.gqa;
+  uint16_t* orow = p.out + (((int64_t)b * p.chunk + r / p.gqa) * Hq + h * p.gqa + r % p.gqa) * D;
+  *reinterpret_cast<uint2*>(orow + 4 * chunk) =
+      make_uint2(pack_bf16(A[0] * inv, A[1] * inv), pack_bf16(A[2] * inv, A[3] * inv));
 }
 
-int32_t tg_prefill(const tg_prefill_args* a, void* hip_stream) {
+size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// Workspace of the key-split launch for this shape, 0 where it is not taken.
+struct SplitLayout {
+  int row_tiles, part_waves, groups;
+  size_t o_bytes, ml_bytes, bytes;
+};
+
+SplitLayout split_layout(const tg_geometry& g, int batch, int chunk_len) {
+  SplitLayout s = {};
+  const int64_t rows = (int64_t)chunk_len * (g.num_q_heads / g.num_kv_heads);
+  const int64_t row_tiles = (rows + kRows - 1) / kRows;
+  const int64_t units = (int64_t)batch * g.num_kv_heads;
+  if (units > kSplitMaxUnits || units * row_tiles > kSplitMaxBlocks) return s;
+  s.row_tiles = (int)row_tiles;
+  s.part_waves = (int)((rows < kRows ? rows : kRows) + 31) / 32;
+  s.groups = split_target(g.head_dim) / s.row_tiles + (int)units;   // sum over units of ceil(n / T)
+  const size_t parts = (size_t)split_slots(g.head_dim) * s.part_waves;
+  s.o_bytes = align256(parts * 32 * g.head_dim * sizeof(float));
+  s.ml_bytes = align256(parts * 64 * sizeof(float));
+  s.bytes = s.o_bytes + s.ml_bytes + align256((size_t)(units * row_tiles) * sizeof(int2));
+  return s;
+}
+
+int32_t check_prefill(const tg_prefill_args* a) {
   if (!a) return tg::fail(TG_ERR_INVALID_ARG, "args is NULL");
   const tg_geometry& g = a->geom;
   if (int32_t rc = tg::check_geometry(&g)) return rc;
@@ -437,6 +653,22 @@ int32_t tg_prefill(const tg_prefill_args* a, void* hip_stream) {
   if (gqa < 1 || gqa > 16) return tg::fail(TG_ERR_UNSUPPORTED, "prefill supports 1..16 query heads per KV head");
   if (a->batch < 1 || a->chunk_len < 1 || a->layer < 0 || a->layer >= g.num_layers)
     return tg::fail(TG_ERR_INVALID_ARG, "batch and chunk_len must be >= 1, layer in range");
+  return TG_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+size_t tg_prefill_workspace_bytes(const tg_prefill_args* args) {
+  if (check_prefill(args) != TG_OK) return 0;
+  return split_layout(args->geom, args->batch, args->chunk_len).bytes;
+}
+
+int32_t tg_prefill(const tg_prefill_args* a, void* hip_stream) {
+  if (int32_t rc = check_prefill(a)) return rc;
+  const tg_geometry& g = a->geom;
+  const int gqa = g.num_q_heads / g.num_kv_heads;
   if (!a->q || !a->k_new || !a->v_new || !a->kv_pool || !a->pt_pages || !a->pt_offsets || !a->kv_len ||
       !a->group_of || !a->slot_of || !a->out)
     return tg::fail(TG_ERR_INVALID_ARG, "NULL device pointer");
@@ -468,8 +700,30 @@ int32_t tg_prefill(const tg_prefill_args* a, void* hip_stream) {
   const int units = a->batch * g.num_kv_heads;
   if (a->block_order && a->num_blocks < 1) return tg::fail(TG_ERR_INVALID_ARG, "block_order needs num_blocks >= 1");
   const int blocks = a->block_order ? a->num_blocks : 8 * ((units + 7) / 8) * p.row_tiles;
-  auto kernel = g.head_dim == 128 ? tg_prefill_kernel<128> : tg_prefill_kernel<64>;
-  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, static_cast<hipStream_t>(hip_stream), p);
+  hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  const SplitLayout sl = split_layout(g, a->batch, a->chunk_len);
+  if (sl.bytes > 0 && a->workspace && a->workspace_bytes >= sl.bytes && tg::aligned16({a->workspace})) {
+    char* ws = static_cast<char*>(a->workspace);
+    p.part_o = reinterpret_cast<f32x4*>(ws);
+    p.part_ml = reinterpret_cast<float*>(ws + sl.o_bytes);
+    p.pieces = reinterpret_cast<int2*>(ws + sl.o_bytes + sl.ml_bytes);
+    p.part_waves = sl.part_waves;
+    p.last_tiles = (a->chunk_len - 1 + kTile) / kTile;
+    auto split = g.head_dim == 128 ? tg_prefill_kernel<128, true, 2> : tg_prefill_kernel<64, true, 4>;
+    auto merge = g.head_dim == 128 ? tg_prefill_merge_kernel<128> : tg_prefill_merge_kernel<64>;
+    hipLaunchKernelGGL(split, dim3((sl.groups + 7) / 8 * 8 * sl.row_tiles), dim3(kBlock), 0, st, p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "prefill launch failed: %s", hipGetErrorString(e));
+    hipLaunchKernelGGL(merge, dim3(units * p.row_tiles, sl.part_waves * (g.head_dim / 32)), dim3(256), 0, st, p);
+    e = hipGetLastError();
+    if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "prefill merge launch failed: %s", hipGetErrorString(e));
+    return TG_OK;
+  }
+  // head_dim 64: two workgroups fit a CU (64 KiB rings) at 128 registers, which
+  // pays once there are more than two blocks per CU
+  auto kernel = g.head_dim == 128 ? tg_prefill_kernel<128, false, 2>
+                                  : (blocks > 512 ? tg_prefill_kernel<64, false, 4> : tg_prefill_kernel<64, false, 2>);
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, st, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "prefill launch failed: %s", hipGetErrorString(e));
   return TG_OK;

@@ -126,6 +126,81 @@ def test_prefill_long_chunk_sampled():
     rows.append((int(np.argmax(tables.kv_len[:, 0].max(axis=1))), int(np.argmax(tables.kv_len[:, 0].max(axis=0))) * g.gqa))
     _compare(ps, sorted(set(rows)), "long chunk")
 
+def _give_workspace(ps):
+    """The key-split launch's workspace, whether or not the session expects it to pay; False where there is none."""
+    from paper_2606_06302_amd import tangram as tg
+    n = tg.tg_prefill_workspace_bytes(ps.args)
+    ps.workspace = torch.empty(n, dtype=torch.uint8, device="cuda")
+    ps.args.workspace, ps.args.workspace_bytes = (ps.workspace.data_ptr(), n) if n else (None, 0)
+    return n > 0
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("B,H,Hp,gqa,C,ctx,hist", [
+    (1, 2, 1, 4, 512, 6000, None),              # long blocks cut into many pieces; pieces of chunk keys only
+    (1, 2, 2, 1, 300, 300, 0),                  # no history: the cuts fall between the chunk's own tiles
+    (1, 1, 1, 16, 1, 64 * 700, None),           # one row tile of 16 rows, hundreds of pieces
+    (3, 8, 4, 5, 77, (1, 3000), None),          # odd rows, partial last tiles, unequal units
+    (2, 4, 2, 8, 33, 40, 1),                    # one or two tiles per unit: nothing to cut
+    (64, 8, 2, 1, 5, (30, 200), None),          # 512 units, the most the key-split launch takes
+    (65, 8, 2, 1, 5, (30, 200), None),          # 520 units: whole blocks
+])
+def test_prefill_key_split_edges(d, B, H, Hp, gqa, C, ctx, hist):
+    """The key-split launch (taken when a workspace is given and the blocks are few) and the whole-block launch
+    (the same call without a workspace) against the oracle, NaN in every pool row past the histories; repeated
+    calls on one workspace give the same bits."""
+    _gpu()
+    g = Geometry(1, H, H * gqa, d, 16, Hp)
+    wl = custom(670 + C + B, g, B, "bf16", ctx, chunk_len=C)
+    tables = Tables(wl)
+    pool = torch.from_numpy(poisoned_host_pool(wl, tables)).to(torch.bfloat16).cuda()
+    hist_len = None if hist is None else np.minimum(tables.kv_len, hist)
+    ps = PrefillSession(wl, tables=tables, fill="host", pool=pool, hist_len=hist_len)
+    split = _give_workspace(ps)
+    assert split == (B * H <= 512)
+    say(f"key split d={d} B={B} H={H} gqa={gqa} C={C} workspace {ps.args.workspace_bytes}")
+    rows = [(b, q) for b in (range(B) if B < 10 else (0, 1, B // 2, B - 1)) for q in range(g.num_q_heads)]
+    rows = rows if C < 300 else rows[::3] + rows[-1:]
+    outs = []
+    for _ in range(2):
+        if split:
+            ps.workspace.fill_(0xFF)             # NaN partials: nothing unwritten is read
+        ps.out.fill_(float("nan"))
+        ps.run()
+        torch.cuda.synchronize()
+        outs.append(ps.out.clone())
+    assert torch.equal(outs[0], outs[1])
+    _compare(ps, rows, "key split" if split else "whole blocks")
+    if split:
+        ps.args.workspace, ps.args.workspace_bytes = None, 0
+        ps.out.fill_(float("nan"))
+        ps.run()
+        torch.cuda.synchronize()
+        _compare(ps, rows, "whole blocks")
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_prefill_key_split_clamps_lengths(d):
+    """The key-split launch cuts by the clamped lengths: past the table and below zero as in the whole-block launch."""
+    _gpu()
+    g = Geometry(1, 4, 16, d, 16, 2)
+    wl = custom(653, g, 2, "bf16", (100, 1500), chunk_len=40)
+    tables = Tables(wl)
+    cap = np.zeros_like(tables.kv_len)
+    for b in range(wl.batch):
+        for h in range(g.num_kv_heads):
+            t = b * g.num_groups + int(tables.group_of[0, h])
+            cap[b, 0, h] = (int(tables.pt_offsets[t + 1]) - int(tables.pt_offsets[t])) * g.page_size
+    raw = tables.kv_len.copy()
+    raw[0, 0, :3] = cap[0, 0, :3] + np.array([1, 1000, 2 ** 30])
+    raw[1, 0, :2] = [-5, np.iinfo(np.int32).min]
+    ps = PrefillSession(wl, tables=tables, fill="host", hist_len=np.clip(raw, 0, cap).astype(np.int32))
+    assert _give_workspace(ps)
+    ps.d_kv_len.copy_(torch.from_numpy(raw))       # the device sees the raw lengths, the oracle the clamped ones
+    ps.run()
+    torch.cuda.synchronize()
+    _compare(ps, [(b, q) for b in range(wl.batch) for q in range(g.num_q_heads)], "clamped lengths, key split")
+
 
 @pytest.mark.parametrize("plan", ["fill", "aot"])
 def test_prefill_chunk_of_one_matches_decode_path(plan):
