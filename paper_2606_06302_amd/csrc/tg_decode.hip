@@ -378,45 +378,56 @@ __global__ void __launch_bounds__(kBlock) tg_decode_kernel(DecodeParams p, const
 }
 
 // ---------------------------------------------------------------------------
-// Fast path for bf16 and head_dim 128, any gqa G in 1..16: matrix cores.
+// bf16, head_dim D = 64 or 128, any gqa G in 1..16: matrix cores.
 //
 // Every wave is an independent worker: bin 4*blockIdx.x + wave of the plan.
 // There is no barrier and no cross-wave merge; a wave runs its bin's items one
-// after the other, page by page.
+// after the other in steps of 128/D pages (8 KiB: one page of 16 tokens at
+// head_dim 128, two pages at 64; the last step of an item of odd pages reads
+// its one page twice and masks the second).
 //
-// Data movement.  Pages stream from HBM straight into a ring of R page buffers
+// Data movement.  Steps stream from HBM straight into a ring of R buffers
 // in the wave's own LDS with gfx950's global_load_lds_dwordx4 (no staging
-// registers): page k+R-1 is issued before page k is computed, so R-1 pages
+// registers): step k+R-1 is issued before step k is computed, so R-1 steps
 // (8 KiB each) stay in flight while the wave computes.  The DMA is issued from
 // inline assembly, invisible to the compiler's wait-count pass (which would
 // otherwise drain every load before each LDS read), and the wave waits for
-// page k with an explicit vmcnt that counts the DMA instructions issued after
+// step k with an explicit vmcnt that counts the DMA instructions issued after
 // it; any other vector memory operation issued later (output stores) only
 // makes that wait stricter.  Page ids and work items are read through the
 // constant address space, i.e. with scalar loads, which the vector memory
-// counter does not see.  The queries of an item are DMA'd with its first page
+// counter does not see.  The queries of an item are DMA'd with its first step
 // into one of R-1 per-wave q slots and moved to registers when the item starts.
 //
 // Arithmetic, per 16-token page, with the query heads of the KV head as the
 // 16 columns of the MFMA tiles (columns past G repeat a real head and are
 // never stored):
-//   * S^T[16 tok][16 heads] = K q^T: 4 x v_mfma_f32_16x16x32_bf16, A = K rows
+//   * S^T[16 tok][16 heads] = K q^T: D/32 x v_mfma_f32_16x16x32_bf16, A = K rows
 //     read from LDS (16 bytes per lane), B = q from registers.  Lane
 //     (col, rb) = (lane % 16, lane / 16) receives tokens 4rb..4rb+3 of head col.
-//   * online softmax on those 4 values per lane; the row max and sum of a head
+//   * online softmax on a step's 4 (or 8) values per lane; the row max and sum of a head
 //     combine the 4 lanes of its column with the gfx950 permlane swaps.  The
-//     running max is only raised when a page exceeds it by more than 8 (in
+//     running max is only raised when a step exceeds it by more than 8 (in
 //     log2 units), so rescales are rare and p stays <= 2^8.
-//   * O^T[16 dims][16 heads] += V^T P^T: 8 x v_mfma_f32_16x16x16_bf16, one per
-//     16 dims.  P^T is the S^T tile of the same lane rounded to bf16 (the
+//   * O^T[16 dims][16 heads] += V^T P^T, one product per 16 dims: 16 tokens deep
+//     (v_mfma_f32_16x16x16_bf16) at head_dim 128, 32 deep (16x16x32, k index
+//     8rb+i = token 4rb+i of the first page, then of the second) at 64, there
+//     once with P rounded to bf16 and once with the rest, so that P counts to
+//     2^-17.  P^T is the S^T tile of the same lane rounded to bf16 (the
 //     result layout of the first product is the operand layout of the second),
 //     and V^T comes from LDS with ds_read_b64_tr_b16, whose 4x4 lane transpose
 //     turns row-major V rows into the 4-consecutive-token operand.
-//   * LDS layout: chunk c (16 bytes) of token row r sits at position c ^ r in
-//     the K slab and at c ^ (2r mod 16) in the V slab (the DMA lanes pick their
-//     source chunk accordingly), so both operand reads are bank-conflict free.
+//   * LDS layout: chunk c (16 bytes) of token row r sits at position c ^ k_swz(r)
+//     in the K slab and at c ^ v_swz(r) in the V slab (the DMA lanes pick their
+//     source chunk accordingly), so both operand reads are bank-conflict free:
+//     r and 2r mod 16 with 256-byte rows; with 128-byte rows, where two rows
+//     fill the 64 banks, (r/2) mod 8 and 2((r/2) mod 4).
 // The accumulator of a lane belongs to one head, so rescaling and the final
 // normalisation need no cross-lane traffic.
+//
+// Bound by HBM.  At head_dim 64 a page holds half the bytes for the same
+// softmax; two pages per step keep the wave's instructions per byte near those
+// at 128.  TODO
 constexpr int kFastWorkers = kWaves;   // bins per workgroup in the fast path
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -481,6 +492,11 @@ __device__ __forceinline__ f32x4 mfma_qk(const u4& a, const u4& b, const f32x4& 
 __device__ __forceinline__ f32x4 mfma_pv(const s16x4& a, const s16x4& b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
+// 8 k-values of an operand from two halves of 4
+__device__ __forceinline__ u4 join(const s16x4& lo, const s16x4& hi) {
+  const uint2 a = __builtin_bit_cast(uint2, lo), b = __builtin_bit_cast(uint2, hi);
+  return u4{a.x, a.y, b.x, b.y};
+}
 // Lane l of each 16-lane block receives element l % 4 of the 8-byte rows
 // addressed by lanes l/4, l/4 + 4, l/4 + 8, l/4 + 12 of the block.
 __device__ __forceinline__ s16x4 lds_read_tr16(const void* ptr) {
@@ -490,20 +506,26 @@ __device__ __forceinline__ s16x4 lds_read_tr16(const void* ptr) {
 // This file is built with -mllvm -amdgpu-mfma-vgpr-form: the accumulators stay
 // in VGPRs, where the rescale multiplies them in place, instead of being
 // copied between AGPRs and VGPRs on every page.
-template <int QMAX>   // 8 or 16: the q slots hold up to QMAX query heads
+template <int D, int QMAX>   // QMAX 8 or 16: the q slots hold up to QMAX query heads
 __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, const tg_work_item* __restrict__ items_g,
                                                                const int32_t* __restrict__ pt_g,
                                                                const int32_t* __restrict__ bin_offsets_g,
                                                                const u4* __restrict__ pool) {
-  constexpr int D = 128;
-  constexpr int R = QMAX <= 8 ? 4 : 3;   // LDS page buffers per wave
+  static_assert(D == 64 || D == 128, "head_dim 64 or 128");
+  constexpr int KP = 128 / D;            // pages per step
+  constexpr int kStep = KP * kPage;      // tokens per step
+  constexpr int CPR = D / 8;             // 16-byte chunks per row
+  constexpr int kSlab = kPage * CPR;     // chunks per K or V slab of a page
+  constexpr int R = QMAX * D <= 1024 ? 4 : 3;   // LDS step buffers per wave (160 KiB a CU)
   constexpr int NQ = R - 1;              // LDS query buffers per wave
-  constexpr int kQChunks = QMAX * (D / 8);
-  constexpr int kDma = 8;                // DMA instructions per page: 4 K + 4 V
+  constexpr int kQChunks = QMAX * CPR;
+  constexpr int kDma = 8;                // DMA instructions per step: 4 K + 4 V
   constexpr float kSlack = 8.0f;
-  static_assert(kPage == 16, "one page is one 4 KiB K slab and one 4 KiB V slab");
+  static_assert(kPage == 16 && KP * kSlab == 256, "one step is 4 KiB of K and 4 KiB of V");
+  auto k_swz = [](int r) { return D == 128 ? r & 15 : (r >> 1) & 7; };
+  auto v_swz = [](int r) { return D == 128 ? (2 * r) & 15 : 2 * ((r >> 1) & 3); };
 
-  __shared__ u4 sm_ring[kWaves][R][512];   // page: K slab, then V slab
+  __shared__ u4 sm_ring[kWaves][R][512];   // step: K slabs, then V slabs
   __shared__ u4 sm_q[kWaves][NQ][kQChunks];
 
   const TG_CONST tg_work_item* const items = (const TG_CONST tg_work_item*)items_g;
@@ -531,12 +553,12 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
   const uint32_t ring_lds = lds_address(&sm_ring[wave][0][0]);
   const uint32_t q_lds = lds_address(&sm_q[wave][0][0]);
   const u4* const qsrc = static_cast<const u4*>(p.q);
-  const int nq = G * (D / 8);           // 16-byte chunks of one item's queries
+  const int nq = G * CPR;               // 16-byte chunks of one item's queries
 
-  // DMA cursor over every page of every item of the bin; it caches the
-  // item's page count, table base, slot and query offset.
+  // DMA cursor over every step of every item of the bin (pi: step, ns: steps);
+  // it caches the item's page count, table base, slot and query offset.
   struct Cursor {
-    int it, pi, np, slot, arow;
+    int it, pi, ns, np, slot, arow;
     int64_t pbase, qoff;
   };
   auto enter = [&](Cursor& cu, int it) {
@@ -545,13 +567,14 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
     cu.it = it;
     cu.pi = 0;
     cu.np = (im.tok_end - im.tok_begin + kPage - 1) / kPage;
+    cu.ns = (cu.np + KP - 1) / KP;
     cu.slot = im.slot;
-    cu.arow = arow >= 0 ? arow & (kPage - 1) : -1;   // row of the last page that takes the new token
+    cu.arow = arow >= 0 ? (arow - im.tok_begin) % kStep : -1;   // row of the last step that takes the new token
     cu.pbase = im.pt_base + im.tok_begin / kPage;
-    cu.qoff = ((int64_t)im.b * p.num_q_heads + (int64_t)im.kv_head * G) * (D / 8);
+    cu.qoff = ((int64_t)im.b * p.num_q_heads + (int64_t)im.kv_head * G) * CPR;
   };
   auto advance = [&](Cursor& cu) {   // false (cursor unchanged) past the bin's last page
-    if (cu.pi + 1 < cu.np) {
+    if (cu.pi + 1 < cu.ns) {
       ++cu.pi;
       return true;
     }
@@ -561,8 +584,18 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
     }
     return false;
   };
-  // queries (on an item's first page), then the page's K slab, then its V slab
-  auto issue = [&](const Cursor& cu, int32_t id, int ring) {
+  // page ids of the cursor's step (an odd item's last page twice)
+  struct Ids {
+    int32_t v[KP];
+  };
+  auto page_ids = [&](const Cursor& cu) {
+    Ids r;
+#pragma unroll
+    for (int k = 0; k < KP; ++k) r.v[k] = pt[cu.pbase + (KP == 1 ? cu.pi : min(KP * cu.pi + k, cu.np - 1))];
+    return r;
+  };
+  // queries (on an item's first step), then the step's K slabs, then its V slabs
+  auto issue = [&](const Cursor& cu, const Ids& id, int ring) {
     if (cu.pi == 0) {
       const u4* qb = qsrc + cu.qoff;
       const uint32_t dst = q_lds + ((cu.it - it_begin) % NQ) * (kQChunks * 16);
@@ -570,89 +603,90 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
       for (int j = 0; j < kQChunks / 64; ++j)
         if (j * 64 < nq) lds_dma16(qb + min(j * 64 + lane, nq - 1), dst + j * 1024);
     }
-    const u4* base = pool + (int64_t)id * p.page_chunks;
-    const u4* kb = base + cu.slot * 256;
-    const u4* vb = base + (p.heads_per_group + cu.slot) * 256;
+    constexpr int kPerPage = 4 / KP;       // 1 KiB instructions per slab
+    constexpr int kRowsPerDma = 64 / CPR;
     const uint32_t dst = ring_lds + ring * 8192;
-    if (cu.arow >= 0 && cu.pi == cu.np - 1) {   // the page that takes the new token: that row from the token
-      const int64_t toff = ((int64_t)items[cu.it].b * p.num_kv_heads + items[cu.it].kv_head) * (D / 8);
+    const int pos = lane % CPR;            // chunk position within the row
+    if (cu.arow >= 0 && cu.pi == cu.ns - 1) {   // the step that takes the new token: that row from the token
+      const int64_t toff = ((int64_t)items[cu.it].b * p.num_kv_heads + items[cu.it].kv_head) * CPR;
       const u4* tk = p.append_k + toff;
       const u4* tv = p.append_v + toff;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int r = j * 4 + (lane >> 4);
-        const int pos = lane & 15;
-        lds_dma16(r == cu.arow ? tk + (pos ^ r) : kb + r * 16 + (pos ^ r), dst + j * 1024);
+        const u4* kb = pool + (int64_t)id.v[j / kPerPage] * p.page_chunks + cu.slot * kSlab;
+        const int r = (j % kPerPage) * kRowsPerDma + lane / CPR;   // token row of the page
+        const int c = pos ^ k_swz(r);
+        lds_dma16((j / kPerPage) * kPage + r == cu.arow ? tk + c : kb + r * CPR + c, dst + j * 1024);
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int r = j * 4 + (lane >> 4);
-        const int pos = lane & 15;
-        const int c = pos ^ ((2 * r) & 15);
-        lds_dma16(r == cu.arow ? tv + c : vb + r * 16 + c, dst + 4096 + j * 1024);
+        const u4* vb = pool + (int64_t)id.v[j / kPerPage] * p.page_chunks + (p.heads_per_group + cu.slot) * kSlab;
+        const int r = (j % kPerPage) * kRowsPerDma + lane / CPR;
+        const int c = pos ^ v_swz(r);
+        lds_dma16((j / kPerPage) * kPage + r == cu.arow ? tv + c : vb + r * CPR + c, dst + 4096 + j * 1024);
       }
       return;
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int r = j * 4 + (lane >> 4);   // token row written by this lane
-      const int pos = lane & 15;           // chunk position within the row
-      lds_dma16(kb + r * 16 + (pos ^ r), dst + j * 1024);
+      const u4* kb = pool + (int64_t)id.v[j / kPerPage] * p.page_chunks + cu.slot * kSlab;
+      const int r = (j % kPerPage) * kRowsPerDma + lane / CPR;   // token row of the page, written by this lane
+      lds_dma16(kb + r * CPR + (pos ^ k_swz(r)), dst + j * 1024);
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int r = j * 4 + (lane >> 4);
-      const int pos = lane & 15;
-      lds_dma16(vb + r * 16 + (pos ^ ((2 * r) & 15)), dst + 4096 + j * 1024);
+      const u4* vb = pool + (int64_t)id.v[j / kPerPage] * p.page_chunks + (p.heads_per_group + cu.slot) * kSlab;
+      const int r = (j % kPerPage) * kRowsPerDma + lane / CPR;
+      lds_dma16(vb + r * CPR + (pos ^ v_swz(r)), dst + 4096 + j * 1024);
     }
   };
 
   Cursor d;
   enter(d, it_begin);
   bool d_live = true;
-  int32_t d_id = pt[d.pbase];
+  Ids d_id = page_ids(d);
 #pragma unroll
   for (int r = 0; r < R - 1; ++r) {
     if (d_live) {
       issue(d, d_id, r);
       d_live = advance(d);
-      if (d_live) d_id = pt[d.pbase + d.pi];
+      if (d_live) d_id = page_ids(d);
     }
   }
 
   // lane-constant parts of the operand addresses
-  const int k_off = col * 16;                                  // A of q.k: token row col
+  const int k_off = col * CPR;                                 // A of q.k: token row col
   const int v_tok = lane >> 2;                                 // source row of the transposed read
-  const int v_off = 4096 + v_tok * 256 + (lane & 3) * 8;       // bytes within the page buffer
-  const int v_swz = v_tok & 7;
+  const int v_off = 4096 + v_tok * (CPR * 16) + (lane & 3) * 8;   // bytes within the step buffer
+  const int v_x = v_swz(v_tok) >> 1;                           // 32-byte pairs of chunks are swizzled as one
 
-  int it = it_begin, pi = 0, np = 0, ntok = 0, k = 0, arow = -1;
+  int it = it_begin, pi = 0, ns = 0, ntok = 0, k = 0, arow = -1;
   tg_work_item item;
-  u4 qv[4];
+  u4 qv[D / 32];
   float m = -INFINITY, l = 0.f;
-  f32x4 acc[8];
+  f32x4 acc[D / 16];
   for (;;) {
-    if (pi == 0) {   // item start: its queries were DMA'd just before its first page
+    if (pi == 0) {   // item start: its queries were DMA'd just before its first step
       item = load_item(items + it, p, &arow);
       ntok = item.tok_end - item.tok_begin;
-      np = (ntok + kPage - 1) / kPage;
+      ns = (ntok + kStep - 1) / kStep;
       if (d_live)
         wait_vmcnt<kDma * (R - 1)>();
       else
         wait_vmcnt<0>();
-      const u4* qrow = &sm_q[wave][(it - it_begin) % NQ][hq * 16 + rb];
+      const u4* qrow = &sm_q[wave][(it - it_begin) % NQ][hq * CPR + rb];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) qv[c] = qrow[4 * c];
+      for (int c = 0; c < D / 32; ++c) qv[c] = qrow[4 * c];
       wait_lgkmcnt0();   // the slot may be refilled by the DMA issued next
       m = -INFINITY;
       l = 0.f;
 #pragma unroll
-      for (int mm = 0; mm < 8; ++mm) acc[mm] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int mm = 0; mm < D / 16; ++mm) acc[mm] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    if (d_live) {   // keep R-1 pages in flight: issue page k+R-1, then wait for page k
+    if (d_live) {   // keep R-1 steps in flight: issue step k+R-1, then wait for step k
       issue(d, d_id, (k + R - 1) % R);
       d_live = advance(d);
-      if (d_live) d_id = pt[d.pbase + d.pi];
+      if (d_live) d_id = page_ids(d);
       wait_vmcnt<kDma * (R - 1)>();
     } else {
       wait_vmcnt<0>();
@@ -660,16 +694,21 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
     const int rs = k % R;
     const u4* const kbuf = &sm_ring[wave][rs][0];
     const char* const pbuf = reinterpret_cast<const char*>(&sm_ring[wave][rs][0]);
-    const int nvalid = min(kPage, ntok - pi * kPage);
+    const int nvalid = min(kStep, ntok - pi * kStep);
 
     // S^T = K q^T
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    float sv[4 * KP];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) s = mfma_qk(kbuf[k_off + ((4 * c + rb) ^ col)], qv[c], s);
-    float sv[4];
+    for (int t = 0; t < KP; ++t) {
+      f32x4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sv[i] = 4 * rb + i < nvalid ? s[i] : -INFINITY;
-    float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
+      for (int c = 0; c < D / 32; ++c) s = mfma_qk(kbuf[t * kSlab + k_off + ((4 * c + rb) ^ k_swz(col))], qv[c], s);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sv[4 * t + i] = t * kPage + 4 * rb + i < nvalid ? s[i] : -INFINITY;
+    }
+    float mx = sv[0];
+#pragma unroll
+    for (int i = 1; i < 4 * KP; ++i) mx = fmaxf(mx, sv[i]);
     mx = swap32_max(swap16_max(mx));
     const bool raise = (mx - m) * cs > kSlack;
     if (__any(raise)) {
@@ -678,43 +717,56 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
       l *= alpha;
       m = m_new;
 #pragma unroll
-      for (int mm = 0; mm < 8; ++mm) acc[mm] *= alpha;
+      for (int mm = 0; mm < D / 16; ++mm) acc[mm] *= alpha;
     }
     const float mcs = m * cs;
-    s16x4 pb;
+    s16x4 pb[KP], pl[KP];   // P rounded to bf16, and (head_dim 64) what the rounding left
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 4 * KP; ++i) {
       const float pk = fast_exp2(fmaf(sv[i], cs, -mcs));
       l += pk;
-      pb[i] = (short)f32_to_bf16(pk);
+      const uint16_t hi = f32_to_bf16(pk);
+      pb[i / 4][i % 4] = (short)hi;
+      if constexpr (KP == 2) pl[i / 4][i % 4] = (short)f32_to_bf16(pk - __uint_as_float((uint32_t)hi << 16));
     }
     // O^T += V^T P^T
-    const bool partial = nvalid < kPage;
+    const bool partial = nvalid < kStep;
 #pragma unroll
-    for (int mm = 0; mm < 8; ++mm) {
-      s16x4 a = lds_read_tr16(pbuf + v_off + ((mm ^ v_swz) << 5));
-      if (partial) {   // rows past the retained length may hold anything
+    for (int mm = 0; mm < D / 16; ++mm) {
+      s16x4 a[KP];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (4 * rb + j >= nvalid) a[j] = 0;
+      for (int t = 0; t < KP; ++t) {
+        a[t] = lds_read_tr16(pbuf + v_off + t * (kSlab * 16) + ((mm ^ v_x) << 5));
+        if (partial) {   // rows past the retained length may hold anything
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (t * kPage + 4 * rb + j >= nvalid) a[t][j] = 0;
+        }
       }
-      acc[mm] = mfma_pv(a, pb, acc[mm]);
+      if constexpr (KP == 1) {
+        acc[mm] = mfma_pv(a[0], pb[0], acc[mm]);
+      } else {
+        const u4 v = join(a[0], a[1]);
+        acc[mm] = mfma_qk(v, join(pb[0], pb[1]), acc[mm]);
+        acc[mm] = mfma_qk(v, join(pl[0], pl[1]), acc[mm]);
+      }
     }
     ++k;
-    if (++pi < np) continue;
+    if (++pi < ns) continue;
 
     if (arow >= 0) {
       // the new token becomes entry arow of the cache: its rows are in this
-      // page's LDS buffer (refilled only by the next issue), 16 lanes for K
-      // and 16 for V, stored with ordinary vector stores, which the DMA waits
+      // step's LDS buffer (refilled only by the next issue), CPR lanes for K
+      // and CPR for V, stored with ordinary vector stores, which the DMA waits
       // above only count as extra (later) operations
-      const int r = arow & (kPage - 1);
+      const int r = arow % kPage;
       const int64_t pg = (int64_t)pt[item.pt_base + arow / kPage] * p.page_chunks;
-      if (lane < 32) {
-        const int ch = lane & 15;
-        const bool is_k = lane < 16;
-        const u4 row = is_k ? kbuf[r * 16 + (ch ^ r)] : kbuf[256 + r * 16 + (ch ^ ((2 * r) & 15))];
-        p.pool_w[pg + (is_k ? item.slot : p.heads_per_group + item.slot) * 256 + r * 16 + ch] = row;
+      if (lane < 2 * CPR) {
+        const int ch = lane % CPR;
+        const bool is_k = lane < CPR;
+        const int row = ((arow - item.tok_begin) % kStep) * CPR;   // of the step
+        const u4 v = is_k ? kbuf[row + (ch ^ k_swz(r))] : kbuf[256 + row + (ch ^ v_swz(r))];
+        p.pool_w[pg + (is_k ? item.slot : p.heads_per_group + item.slot) * kSlab + r * CPR + ch] = v;
       }
       if (lane == 0) p.live_w[(int64_t)item.b * p.live_stride + item.kv_head] = arow + 1;
     } else if (arow == -2 && lane == 0 && p.append_full) {
@@ -731,19 +783,19 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
         uint2* orow = reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) +
                                                ((int64_t)item.b * p.num_q_heads + qh) * D + 4 * rb);
 #pragma unroll
-        for (int mm = 0; mm < 8; ++mm) {
+        for (int mm = 0; mm < D / 16; ++mm) {
           const f32x4 o = acc[mm] * inv;
           orow[mm * 4] = make_uint2(uint32_t(f32_to_bf16(o[0])) | (uint32_t(f32_to_bf16(o[1])) << 16),
                                     uint32_t(f32_to_bf16(o[2])) | (uint32_t(f32_to_bf16(o[3])) << 16));
         }
         if (p.lse && rb == 0) p.lse[(int64_t)item.b * p.num_q_heads + qh] = lse_nat;
-      } else if (p.merge_counters) {
+      } else if (D == 128 && p.merge_counters) {
         // read in this launch by whichever worker merges the unit, maybe on
         // another XCD: device-scope stores, written through to where every
         // XCD's device-scope loads read
         uint64_t* prow = reinterpret_cast<uint64_t*>(p.part_o + ((int64_t)item.out_idx * G + col) * D + 4 * rb);
 #pragma unroll
-        for (int mm = 0; mm < 8; ++mm) {
+        for (int mm = 0; mm < D / 16; ++mm) {
           const f32x4 o = acc[mm] * inv;
           __hip_atomic_store(prow + mm * 8, pack_f32x2(o[0], o[1]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           __hip_atomic_store(prow + mm * 8 + 1, pack_f32x2(o[2], o[3]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -754,7 +806,7 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
       } else {
         f32x4* prow = reinterpret_cast<f32x4*>(p.part_o + ((int64_t)item.out_idx * G + col) * D + 4 * rb);
 #pragma unroll
-        for (int mm = 0; mm < 8; ++mm) prow[mm * 4] = acc[mm] * inv;
+        for (int mm = 0; mm < D / 16; ++mm) prow[mm * 4] = acc[mm] * inv;
         if (rb == 0) p.part_lse[(int64_t)item.out_idx * G + col] = lse_nat;
       }
     }
@@ -772,7 +824,7 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
   // returned.  This is the ordering a release/acquire pair gives for data
   // written and read by device-scope atomics, without the writeback and
   // invalidation of a whole L2 that a fence for ordinary data needs.
-  if (p.merge_counters) {
+  if constexpr (D == 128) if (p.merge_counters) {
     const TG_CONST int32_t* const unit_splits = (const TG_CONST int32_t*)p.unit_splits;
     const TG_CONST int32_t* const unit_base = (const TG_CONST int32_t*)p.unit_partial_base;
     // the split items of the bin, up to kBatch at a time: all their arrivals
@@ -1058,21 +1110,21 @@ constexpr auto make_decode_table(std::integer_sequence<int, G...>) {
 constexpr int kMaxGqa = 16;
 const std::array<DecodeFn, kMaxGqa> kDecodeF32D64 = make_decode_table<float, 64>(std::make_integer_sequence<int, kMaxGqa>{});
 const std::array<DecodeFn, kMaxGqa> kDecodeF32D128 = make_decode_table<float, 128>(std::make_integer_sequence<int, kMaxGqa>{});
-const std::array<DecodeFn, kMaxGqa> kDecodeBF16D64 = make_decode_table<uint16_t, 64>(std::make_integer_sequence<int, kMaxGqa>{});
 
 DecodeFn pick_decode(int dtype, int d, int gqa) {
   if (gqa < 1 || gqa > kMaxGqa) return nullptr;
-  if (dtype == TG_BF16 && d == 128) return gqa <= 8 ? &tg_decode_mfma_kernel<8> : &tg_decode_mfma_kernel<16>;
+  if (dtype == TG_BF16 && d == 128) return gqa <= 8 ? &tg_decode_mfma_kernel<128, 8> : &tg_decode_mfma_kernel<128, 16>;
+  if (dtype == TG_BF16 && d == 64) return gqa <= 8 ? &tg_decode_mfma_kernel<64, 8> : &tg_decode_mfma_kernel<64, 16>;
   if (dtype == TG_F32 && d == 64) return kDecodeF32D64[gqa - 1];
   if (dtype == TG_F32 && d == 128) return kDecodeF32D128[gqa - 1];
-  if (dtype == TG_BF16 && d == 64) return kDecodeBF16D64[gqa - 1];
   return nullptr;
 }
 
 // bins run by one workgroup of the kernel pick_decode() selects
 int workers_per_wg(int dtype, int d, int gqa) {
+  (void)d;
   (void)gqa;
-  return (dtype == TG_BF16 && d == 128) ? kFastWorkers : 1;
+  return dtype == TG_BF16 ? kFastWorkers : 1;
 }
 
 int32_t check_decode_shape(const tg_geometry* g, int dtype) {

@@ -142,15 +142,14 @@ class DecodeSession:
 
     def workers_per_wg(self):
         """Bins (workers) per workgroup of the decode kernel the library picks for this session:
-        four waves, each its own worker, in the bf16 head-dim-128 kernel; one otherwise."""
-        g = self.wl.geom
-        return 4 if (self.tg_dtype == tg.TG_BF16 and g.head_dim == 128) else 1
+        four waves, each its own worker, in the bf16 kernel; one otherwise."""
+        return 4 if self.tg_dtype == tg.TG_BF16 else 1
 
     def calibrate_xcd_weights(self, stream=None, classes=8, per_layer=False):
         """Measures every worker's pages per microsecond over one stamped step and rebuilds the
         sequential-fill plans with bin weights in proportion to the speed of the worker's class.
-        Worker k runs in workgroup k // w (w = workers_per_wg(): 4 for the bf16 head-dim-128 kernel,
-        else 1); workgroups are dispatched round-robin over the `classes` XCDs, so class =
+        Worker k runs in workgroup k // w (w = workers_per_wg(): 4 for the bf16 kernel, else 1);
+        workgroups are dispatched round-robin over the `classes` XCDs, so class =
         (k // w) % classes.  With per_layer, each layer gets the speeds
         its own stamps show (the pattern differs from layer to layer); else one set pooled over the
         layers.  Returns the relative speeds: [classes], or [layers][classes] with per_layer."""
