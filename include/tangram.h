@@ -233,7 +233,7 @@ int32_t tg_build_plan(const tg_geometry* geom, int32_t batch, int32_t layer, con
  * KV head h = qh / gqa,
  *   O[b][qh] = softmax(K_h q * sm_scale) V_h   over the retained rows of h,
  * executed as the work items of a tg_build_plan partition: worker k of the
- * decode launch (one wave in the bf16 head_dim-128 kernel, one workgroup
+ * decode launch (one wave in the bf16 matrix-core kernel, one workgroup
  * otherwise) runs the items of bin k; an item with out_idx >= 0
  * writes an fp32 partial (o, lse) to the workspace, and the partials of every
  * split unit are combined with a log-sum-exp merge: inside the decode launch

@@ -5,12 +5,12 @@
 // retained rows, stored in the pages of its head group.  The host partition
 // (tg_build_plan, Algorithm 1's proportional rule or the sequential fill)
 // cuts every (b, h) into page-aligned chunks and places them on n_bins bins;
-// worker k of the launch runs bin k (a wave in the matrix-core kernel, a
-// workgroup in the generic one).  A chunk of a split unit writes an fp32
+// worker k of the launch runs bin k (a wave in the bf16 matrix-core kernel, a
+// workgroup in the fp32 one and in the vector kernel, which few bins take).  A chunk of a split unit writes an fp32
 // partial (o, lse), and the partials of every split unit are combined with a
 // log-sum-exp merge (split-KV decoding, Section 2.2.3): by tg_merge_kernel,
 // launched right after on the same stream, or, with arrival counters, inside
-// the matrix-core launch by the piece that finishes last.  The in-launch merge
+// the head_dim-128 bf16 launch by the piece that finishes last.  The in-launch merge
 // orders partials and counters with device-scope stores, loads and atomics
 // only: a fence for ordinary stores would write back and invalidate the whole
 // L2 of an XCD.
@@ -20,9 +20,9 @@
 // themselves: the row is taken from the token buffer instead of the pool,
 // then stored into the pool, and the live length advanced, at the item's end.
 //
-// The generic kernel deals the pages of an item round-robin to the 4 waves of
-// the workgroup; every wave keeps its own online-softmax state and the states
-// are merged through LDS at the end of the item.  The wave index is made
+// The workgroup kernels deal the pages of an item round-robin to their 4 waves;
+// every wave keeps its own online-softmax state and the states are merged
+// through LDS at the end of the item.  The wave index is made
 // wave-uniform (readfirstlane) so that all item/page bookkeeping is scalar.
 #include <hip/hip_runtime.h>
 
@@ -205,8 +205,9 @@ __device__ __forceinline__ void finish_item(const DecodeParams& p, const tg_work
 }
 
 // ---------------------------------------------------------------------------
-// Generic kernel: any head_dim in {64, 128}, fp32 or bf16, 1..16 query heads per
-// KV head.  A page slab (P=16 rows of one head, d*sizeof(T) bytes each) is read
+// Vector kernel for few bins and few query heads (vector_kernel_pays() below):
+// the 4 waves of a workgroup share a bin, and with 1 to 4 query heads per KV
+// head the vector ALU keeps up with them.  A page slab (P=16 rows of one head, d*sizeof(T) bytes each) is read
 // with one 16-byte load per lane per 64 chunks; lane l owns chunk l % CPR of
 // token row l / CPR (CPR = 16-byte chunks per row).  q.k uses v_dot2_f32_bf16
 // on raw bf16 pairs (fp32 FMAs for fp32 data) and a DPP all-reduce over the CPR
@@ -427,8 +428,8 @@ __global__ void __launch_bounds__(kBlock) tg_decode_kernel(DecodeParams p, const
 //
 // Bound by HBM.  At head_dim 64 a page holds half the bytes for the same
 // softmax; two pages per step keep the wave's instructions per byte near those
-// at 128.  TODO
-constexpr int kFastWorkers = kWaves;   // bins per workgroup in the fast path
+// at 128.  32 requests, gqa 4, 2048 to 16384 tokens (182 and 88 MB a layer): 33
+// and 19 us, 5.5 and 4.7 TB/s, against 42 and 26 us on the vector kernel.
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -534,7 +535,7 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
 
   const int lane = threadIdx.x & 63;
   const int wave = wave_id();
-  const int bin = blockIdx.x * kFastWorkers + wave;
+  const int bin = blockIdx.x * (blockDim.x / 64) + wave;   // one to four workers per workgroup
   if (bin >= p.n_bins) return;
   const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
   const int it_begin = bin_offsets[bin], it_end = bin_offsets[bin + 1];
@@ -937,6 +938,278 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
 }
 
 // ---------------------------------------------------------------------------
+// fp32, head_dim D = 64 or 128, any gqa G in 1..16: the fp32 matrix
+// instructions, pages straight from HBM into registers.
+//
+// A workgroup runs one bin.  The pages of an item are dealt round-robin to its
+// 4 waves; every wave keeps its own online-softmax state, merged through LDS at
+// the end of the item.
+//
+// An fp32 operand lane holds one value per product, so any order of the
+// contraction index will do as long as both operands use it, and the lane that
+// loads 16 consecutive bytes feeds four products from them without LDS:
+//   * S^T[16 tok][16 heads] = K q^T: D/4 x v_mfma_f32_16x16x4_f32; lane (col, rb)
+//     = (lane % 16, lane / 16) holds dims 16c + 4rb + i of token col (and of
+//     head col for q) for product (c, i);
+//   * O^T[dims][16 heads] += V^T P^T: product (i, m, j) contracts tokens 4rb + i
+//     for dims 64m + 4col + j: the lane's own S^T value i is the B operand, and
+//     float j of its 16-byte load at dims 64m + 4col of token 4rb + i the A
+//     operand.  The result lane holds dims 64m + 16rb + 4r + j, so j = 0..3 are
+//     again 16 bytes.
+// K's registers are reloaded for the wave's next page as soon as q.k has read
+// them, V's after p.v, so a page is always in flight; page ids are read a page
+// ahead.  The reloads are unconditional (a wave's last page is read once more,
+// from cache): behind a branch the compiler would have to wait for every load
+// in flight before each product (a unit per bin: 168 -> 128 us at head_dim 64).
+// Bound by HBM; the 64 products of a page at head_dim 128 take about 1 us of
+// the 5 a page is given then.  16 requests, gqa 4, 223 MB: 41 us, 5.4 TB/s,
+// against 50 on the vector kernel; gqa 16, 134 MB: 97 -> 36 us with the merge.
+template <int D>
+__global__ void __launch_bounds__(kBlock, 2) tg_decode_f32_kernel(DecodeParams p, const tg_work_item* __restrict__ items_g,
+                                                                 const int32_t* __restrict__ pt_g,
+                                                                 const int32_t* __restrict__ bin_offsets_g,
+                                                                 const u4* __restrict__ pool_g) {
+  static_assert(D == 64 || D == 128, "head_dim 64 or 128");
+  constexpr int CPR = D / 4;             // 16-byte chunks per row
+  constexpr int kSlab = kPage * CPR;     // chunks per K or V slab of a page
+  constexpr int NC = D / 16;             // 16-dim groups of q.k
+  constexpr int NM = D / 64;             // 64-dim groups of p.v
+  constexpr float kSlack = 8.0f;
+
+  __shared__ f32x4 sm_acc[kWaves][16][CPR + 1];   // padded: the rows of different heads on different banks
+  __shared__ f32x4 sm_q[16][CPR + 1];
+  __shared__ float sm_m[kWaves][16], sm_l[kWaves][16];
+
+  const TG_CONST tg_work_item* const items = (const TG_CONST tg_work_item*)items_g;
+  const TG_CONST int32_t* const pt = (const TG_CONST int32_t*)pt_g;
+  const TG_CONST int32_t* const bin_offsets = (const TG_CONST int32_t*)bin_offsets_g;
+  const f32x4* const pool = reinterpret_cast<const f32x4*>(pool_g);
+
+  const int lane = threadIdx.x & 63;
+  const int wave = wave_id();
+  const int G = p.gqa;
+  const int col = lane & 15;
+  const int rb = lane >> 4;
+  const int hq = col < G ? col : col % G;   // columns past G repeat a real head and are never stored
+  const int it_begin = bin_offsets[blockIdx.x], it_end = bin_offsets[blockIdx.x + 1];
+  const float cs = p.scale_log2;
+  const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
+
+  // load cursor over the pages of the bin that are this wave's
+  struct Cursor {
+    int it, pi, np, slot, arow;
+    int64_t pbase;
+  };
+  auto enter = [&](Cursor& cu, int it) {   // the wave's first page at or after item it; false (cursor unchanged) if none
+    for (; it < it_end; ++it) {
+      int arow;
+      const tg_work_item im = load_item(items + it, p, &arow);
+      const int np = (im.tok_end - im.tok_begin + kPage - 1) / kPage;
+      if (wave >= np) continue;
+      cu.it = it;
+      cu.pi = wave;
+      cu.np = np;
+      cu.slot = im.slot;
+      cu.arow = arow >= 0 ? arow % kPage : -1;   // row of the last page that takes the new token
+      cu.pbase = im.pt_base + im.tok_begin / kPage;
+      return true;
+    }
+    return false;
+  };
+  auto advance = [&](Cursor& cu) {   // stays on the wave's last page
+    if (cu.pi + kWaves < cu.np)
+      cu.pi += kWaves;
+    else
+      enter(cu, cu.it + 1);
+  };
+  // every cached row is read once: non-temporal loads
+  f32x4 kc[NC], vc[4][NM];
+  auto load_k = [&](const Cursor& cu, int32_t id) {
+    const bool takes_token = cu.arow >= 0 && cu.pi == cu.np - 1;
+    const f32x4* tok = nullptr;
+    if (takes_token)
+      tok = reinterpret_cast<const f32x4*>(p.append_k) +
+            ((int64_t)items[cu.it].b * p.num_kv_heads + items[cu.it].kv_head) * CPR + rb;
+    const f32x4* src = pool + (int64_t)id * p.page_chunks + cu.slot * kSlab + col * CPR + rb;
+    if (takes_token && col == cu.arow) src = tok;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) kc[c] = __builtin_nontemporal_load(src + 4 * c);
+  };
+  auto load_v = [&](const Cursor& cu, int32_t id) {
+    const bool takes_token = cu.arow >= 0 && cu.pi == cu.np - 1;
+    const f32x4* tok = nullptr;
+    if (takes_token)
+      tok = reinterpret_cast<const f32x4*>(p.append_v) +
+            ((int64_t)items[cu.it].b * p.num_kv_heads + items[cu.it].kv_head) * CPR + col;
+    const f32x4* src = pool + (int64_t)id * p.page_chunks + (p.heads_per_group + cu.slot) * kSlab + 4 * rb * CPR + col;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const f32x4* row = takes_token && 4 * rb + i == cu.arow ? tok : src + i * CPR;
+#pragma unroll
+      for (int m = 0; m < NM; ++m) vc[i][m] = __builtin_nontemporal_load(row + 16 * m);
+    }
+  };
+
+  Cursor d = {};
+  int32_t d_id = 0;
+  if (enter(d, it_begin)) {   // a wave without a page loads nothing and meets the others at the barriers
+    d_id = pt[d.pbase + d.pi];
+    load_k(d, d_id);
+    load_v(d, d_id);
+    advance(d);
+    d_id = pt[d.pbase + d.pi];
+  }
+
+  for (int it = it_begin; it < it_end; ++it) {
+    int arow;   // entry that takes the appended token, or < 0
+    const tg_work_item item = load_item(items + it, p, &arow);
+    const int ntok = item.tok_end - item.tok_begin;
+    const int np = (ntok + kPage - 1) / kPage;
+    {   // the item's queries through LDS: in registers they would cost a wave its second accumulator
+      const f32x4* qrow = reinterpret_cast<const f32x4*>(p.q) +
+                          ((int64_t)item.b * p.num_q_heads + item.kv_head * G) * CPR;
+      for (int o = threadIdx.x; o < G * CPR; o += kBlock) sm_q[o / CPR][o % CPR] = qrow[o];
+      __syncthreads();
+    }
+    const f32x4* const qv = &sm_q[hq][rb];
+    float m = -INFINITY, l = 0.f;
+    f32x4 acc[2][NM][4];   // even and odd tokens, added at the item's end: half the rounding steps in a row
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int mm = 0; mm < NM; ++mm)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[e][mm][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    for (int pi = wave; pi < np; pi += kWaves) {
+      const int nvalid = min(kPage, ntok - pi * kPage);
+      // S^T = K q^T: sums over 8 dims, then a tree: few rounding steps in a row
+      f32x4 s[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const f32x4 q = qv[4 * c];
+        f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          a = __builtin_amdgcn_mfma_f32_16x16x4f32(kc[c][i], q[i], a, 0, 0, 0);
+          b = __builtin_amdgcn_mfma_f32_16x16x4f32(kc[c][i + 2], q[i + 2], b, 0, 0, 0);
+        }
+        s[c] = a + b;
+        if (c % 2 == 1) {
+          s[c - 1] += s[c];
+          __builtin_amdgcn_sched_barrier(0);   // at most two groups' sums at once: registers
+        }
+      }
+#pragma unroll
+      for (int n = 2; n < NC; n *= 2)
+#pragma unroll
+        for (int c = 0; c < NC; c += 2 * n) s[c] += s[c + n];
+      load_k(d, d_id);
+      float sv[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sv[i] = 4 * rb + i < nvalid ? s[0][i] : -INFINITY;
+      float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
+      mx = swap32_max(swap16_max(mx));
+      const bool raise = (mx - m) * cs > kSlack;   // rescale only when it matters: p <= 2^8
+      if (__any(raise)) {
+        const float m_new = raise ? mx : m;
+        const float alpha = fast_exp2((m - m_new) * cs);   // 0 when m was -inf
+        l *= alpha;
+        m = m_new;
+#pragma unroll
+        for (int mm = 0; mm < NM; ++mm)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            acc[0][mm][j] *= alpha;
+            acc[1][mm][j] *= alpha;
+          }
+      }
+      // relative to m itself, not to a rounded m * cs: the state's m is what
+      // the waves' and the pieces' states are weighted by
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        sv[i] = fast_exp2((sv[i] - m) * cs);
+        l += sv[i];
+      }
+      // O^T += V^T P^T
+      const bool partial = nvalid < kPage;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (partial && 4 * rb + i >= nvalid) {   // rows past the retained length may hold anything
+#pragma unroll
+          for (int mm = 0; mm < NM; ++mm) vc[i][mm] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int mm = 0; mm < NM; ++mm)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[i & 1][mm][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[i][mm][j], sv[i], acc[i & 1][mm][j], 0, 0, 0);
+      }
+      load_v(d, d_id);
+      advance(d);
+      d_id = pt[d.pbase + d.pi];
+    }
+
+    // item end: the waves' states through LDS (a wave that saw no row has m =
+    // -inf and weight 0), then the output or this piece's partial
+    l = swap32_sum(swap16_sum(l));
+    if (col < G) {
+#pragma unroll
+      for (int mm = 0; mm < NM; ++mm)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          sm_acc[wave][col][16 * mm + 4 * rb + r] =
+              f32x4{acc[0][mm][0][r] + acc[1][mm][0][r], acc[0][mm][1][r] + acc[1][mm][1][r],
+                    acc[0][mm][2][r] + acc[1][mm][2][r], acc[0][mm][3][r] + acc[1][mm][3][r]};
+      if (rb == 0) {
+        sm_m[wave][col] = m;
+        sm_l[wave][col] = l;
+      }
+    }
+    __syncthreads();
+    for (int o = threadIdx.x; o < G * CPR; o += kBlock) {
+      const int g = o / CPR, c = o % CPR;
+      float M = sm_m[0][g];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) M = fmaxf(M, sm_m[w][g]);
+      float L = 0.f;
+      f32x4 A = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const float f = fast_exp2((sm_m[w][g] - M) * cs);
+        L = fmaf(sm_l[w][g], f, L);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) A[q] = fmaf(sm_acc[w][g][c][q], f, A[q]);
+      }
+      const f32x4 O = {A[0] / L, A[1] / L, A[2] / L, A[3] / L};
+      const int64_t row = item.out_idx < 0 ? (int64_t)item.b * p.num_q_heads + item.kv_head * G + g
+                                           : (int64_t)item.out_idx * G + g;
+      reinterpret_cast<f32x4*>(item.out_idx < 0 ? static_cast<float*>(p.out) : p.part_o)[row * CPR + c] = O;
+      float* lse = item.out_idx < 0 ? p.lse : p.part_lse;
+      if (lse && c == 0) lse[row] = M * p.scale + logf(L);
+    }
+    if (arow >= 0) {   // the token becomes entry arow of the cache; every wave read the length above
+      if (threadIdx.x < 2 * CPR) {
+        const bool is_k = threadIdx.x < CPR;
+        const int ch = threadIdx.x % CPR;
+        const int64_t toff = ((int64_t)item.b * p.num_kv_heads + item.kv_head) * CPR;
+        const int64_t pg = (int64_t)pt[item.pt_base + arow / kPage] * p.page_chunks;
+        p.pool_w[pg + (is_k ? item.slot : p.heads_per_group + item.slot) * kSlab + (arow % kPage) * CPR + ch] =
+            is_k ? p.append_k[toff + ch] : p.append_v[toff + ch];
+      }
+      if (threadIdx.x == 0) p.live_w[(int64_t)item.b * p.live_stride + item.kv_head] = arow + 1;
+    } else if (arow == -2 && threadIdx.x == 0 && p.append_full) {
+      *p.append_full = 1;
+    }
+    __syncthreads();   // the states may be overwritten
+  }
+  if (p.timestamps && threadIdx.x == 0) {   // one lane, vector stores
+    p.timestamps[2 * blockIdx.x] = t_start;
+    p.timestamps[2 * blockIdx.x + 1] = __builtin_amdgcn_s_memrealtime();
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Log-sum-exp merge of the split partials of every unit (b, h) with more than
 // one split: lse* = log sum_i e^{lse_i}, O = sum_i e^{lse_i - lse*} o_i.
 // Grid (units, ceil(gqa*D / 1024)): each thread owns four consecutive output
@@ -1102,29 +1375,52 @@ MergeFn pick_merge(int dtype, int d, int lanes) {
 
 using DecodeFn = void (*)(DecodeParams, const tg_work_item*, const int32_t*, const int32_t*, const u4*);
 
-template <typename T, int D, int... G>
-constexpr auto make_decode_table(std::integer_sequence<int, G...>) {
-  return std::array<DecodeFn, sizeof...(G)>{&tg_decode_kernel<T, D, G + 1>...};
+constexpr int kMaxGqa = 16;
+
+// Where the vector kernel is the faster one: plans of few bins (one worker per
+// unit, say), whose time is that of one worker.  There four waves on a bin, and
+// at few query heads no 16-column matrix tiles, win.  Measured at 128 bins of
+// one unit each (16 requests, 8192 tokens), vector against matrix kernel: bf16
+// head_dim 64, gqa 1 / 4 71 / 133 against 204 / 204 us, gqa 8 (64 bins) 194
+// against 189; f32 gqa 1 107 against 128 (64) and 155 against 214 us (128),
+// gqa 4 194 against 128 and 301 against 213.  At 256 bins of equal shares:
+// bf16 gqa 1 / 4 20 / 31 against 36 / 37 us; at 1024 the matrix kernels win
+// (bf16 23 / 26 against 18 / 19 us).
+bool vector_kernel_pays(int dtype, int d, int gqa, int n_bins) {
+  if (n_bins > 384) return false;
+  return dtype == TG_F32 ? gqa <= 2 : d == 64 && gqa <= 4;
 }
 
-constexpr int kMaxGqa = 16;
-const std::array<DecodeFn, kMaxGqa> kDecodeF32D64 = make_decode_table<float, 64>(std::make_integer_sequence<int, kMaxGqa>{});
-const std::array<DecodeFn, kMaxGqa> kDecodeF32D128 = make_decode_table<float, 128>(std::make_integer_sequence<int, kMaxGqa>{});
+template <typename T, int D>
+DecodeFn pick_vector(int gqa) {
+  if constexpr (sizeof(T) == 4) return gqa == 1 ? &tg_decode_kernel<T, D, 1> : &tg_decode_kernel<T, D, 2>;
+  else
+    return gqa == 1 ? &tg_decode_kernel<T, D, 1>
+                    : gqa == 2 ? &tg_decode_kernel<T, D, 2> : gqa == 3 ? &tg_decode_kernel<T, D, 3> : &tg_decode_kernel<T, D, 4>;
+}
 
-DecodeFn pick_decode(int dtype, int d, int gqa) {
+DecodeFn pick_decode(int dtype, int d, int gqa, int n_bins) {
   if (gqa < 1 || gqa > kMaxGqa) return nullptr;
+  if (vector_kernel_pays(dtype, d, gqa, n_bins)) {
+    if (dtype == TG_BF16) return pick_vector<uint16_t, 64>(gqa);
+    return d == 64 ? pick_vector<float, 64>(gqa) : pick_vector<float, 128>(gqa);
+  }
   if (dtype == TG_BF16 && d == 128) return gqa <= 8 ? &tg_decode_mfma_kernel<128, 8> : &tg_decode_mfma_kernel<128, 16>;
   if (dtype == TG_BF16 && d == 64) return gqa <= 8 ? &tg_decode_mfma_kernel<64, 8> : &tg_decode_mfma_kernel<64, 16>;
-  if (dtype == TG_F32 && d == 64) return kDecodeF32D64[gqa - 1];
-  if (dtype == TG_F32 && d == 128) return kDecodeF32D128[gqa - 1];
+  if (dtype == TG_F32 && d == 64) return &tg_decode_f32_kernel<64>;
+  if (dtype == TG_F32 && d == 128) return &tg_decode_f32_kernel<128>;
   return nullptr;
 }
 
-// bins run by one workgroup of the kernel pick_decode() selects
-int workers_per_wg(int dtype, int d, int gqa) {
-  (void)d;
-  (void)gqa;
-  return dtype == TG_BF16 ? kFastWorkers : 1;
+// Waves per workgroup of the bf16 kernel, each with a bin of its own.  Its LDS
+// limits a CU to one workgroup of up to four waves, so plans of fewer bins than
+// four per CU take fewer waves per workgroup and use every CU: 256 bins, gqa 4,
+// 16 requests of 8192 tokens 60.5 -> 58.2 us at head_dim 128, 38.8 -> 36.6 at
+// 64.
+int waves_per_wg(int n_bins) {
+  constexpr int kCus = 256;
+  const int w = n_bins / kCus + (n_bins % kCus != 0);
+  return w < kWaves ? w : kWaves;
 }
 
 int32_t check_decode_shape(const tg_geometry* g, int dtype) {
@@ -1235,9 +1531,11 @@ int32_t decode_impl(const tg_decode_args* a, void* ws_ptr, size_t ws_bytes, void
   p.scale_log2 = p.scale * kLog2e;
   if (a->num_items == 0) return TG_OK;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  DecodeFn fn = pick_decode(a->dtype, g.head_dim, gqa);
-  const int wpw = workers_per_wg(a->dtype, g.head_dim, gqa);
-  hipLaunchKernelGGL(fn, dim3((a->n_bins + wpw - 1) / wpw), dim3(kBlock), 0, st, p, a->items, a->pt_pages,
+  DecodeFn fn = pick_decode(a->dtype, g.head_dim, gqa, a->n_bins);
+  const bool wave_bins = a->dtype == TG_BF16 && !vector_kernel_pays(a->dtype, g.head_dim, gqa, a->n_bins);
+  const int waves = wave_bins ? waves_per_wg(a->n_bins) : kWaves;
+  const int bins = wave_bins ? waves : 1;   // bins per workgroup
+  hipLaunchKernelGGL(fn, dim3((a->n_bins + bins - 1) / bins), dim3(64 * waves), 0, st, p, a->items, a->pt_pages,
                      a->bin_offsets, p.pool);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "decode launch failed: %s", hipGetErrorString(e));
@@ -1272,7 +1570,7 @@ size_t tg_decode_workspace_bytes(const tg_geometry* geom, int32_t batch, int32_t
 int32_t tg_decode_max_ctas(const tg_geometry* geom, int32_t dtype, int32_t device, int32_t* n_cta) {
   if (!n_cta) return tg::fail(TG_ERR_INVALID_ARG, "n_cta is NULL");
   if (int32_t rc = check_decode_shape(geom, dtype)) return rc;
-  DecodeFn fn = pick_decode(dtype, geom->head_dim, geom->num_q_heads / geom->num_kv_heads);
+  DecodeFn fn = pick_decode(dtype, geom->head_dim, geom->num_q_heads / geom->num_kv_heads, INT32_MAX);
   int cus = 0, per_cu = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
     return tg::fail(TG_ERR_HIP, "hipDeviceGetAttribute failed for device %d", device);
@@ -1282,7 +1580,7 @@ int32_t tg_decode_max_ctas(const tg_geometry* geom, int32_t dtype, int32_t devic
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), kBlock, 0);
   if (prev != device) (void)hipSetDevice(prev);
   if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "occupancy query failed: %s", hipGetErrorString(e));
-  *n_cta = per_cu * cus * workers_per_wg(dtype, geom->head_dim, geom->num_q_heads / geom->num_kv_heads);
+  *n_cta = per_cu * cus * (dtype == TG_BF16 ? kWaves : 1);
   return TG_OK;
 }
 

@@ -141,14 +141,18 @@ class DecodeSession:
         return end - items["tok_begin"]
 
     def workers_per_wg(self):
-        """Bins (workers) per workgroup of the decode kernel the library picks for this session:
-        four waves, each its own worker, in the bf16 kernel; one otherwise."""
-        return 4 if self.tg_dtype == tg.TG_BF16 else 1
+        """Bins (workers) per workgroup of the decode kernel the library picks for this session: in the
+        bf16 kernel up to four waves, each its own worker (fewer for plans of under four bins per CU);
+        one otherwise (fp32, and head_dim 64 with few bins and query heads)."""
+        g = self.wl.geom
+        if self.tg_dtype != tg.TG_BF16 or (g.head_dim == 64 and g.gqa <= 4 and self.n_bins <= 384):
+            return 1
+        return min(4, -(-self.n_bins // 256))
 
     def calibrate_xcd_weights(self, stream=None, classes=8, per_layer=False):
         """Measures every worker's pages per microsecond over one stamped step and rebuilds the
         sequential-fill plans with bin weights in proportion to the speed of the worker's class.
-        Worker k runs in workgroup k // w (w = workers_per_wg(): 4 for the bf16 kernel, else 1);
+        Worker k runs in workgroup k // w (w = workers_per_wg());
         workgroups are dispatched round-robin over the `classes` XCDs, so class =
         (k // w) % classes.  With per_layer, each layer gets the speeds
         its own stamps show (the pattern differs from layer to layer); else one set pooled over the

@@ -325,6 +325,22 @@ def test_fused_merge_matches_two_launch_merge_bitwise(gqa, mode, n_bins, st):
         compare_layer(fused, l, what=f"fused merge layer {l}")
 
 
+@pytest.mark.parametrize("dtype,d,gqa", [("bf16", 64, 1), ("bf16", 64, 4), ("bf16", 64, 8), ("bf16", 64, 9),
+                                         ("bf16", 64, 16), ("f32", 64, 2), ("f32", 64, 5), ("f32", 64, 16),
+                                         ("f32", 128, 1), ("f32", 128, 7), ("f32", 128, 16), ("bf16", 128, 8)])
+@pytest.mark.parametrize("mode,n_bins", [(3, 384), (3, 385), (3, 700), (3, 1025), (0, 500), (1, None)])
+def test_kernel_choice_edges(dtype, d, gqa, mode, n_bins):
+    """Units around one and two 16-token pages (the matrix kernels' tiles, and the two-page steps of bf16 head_dim
+    64) and around 4 waves' pages, on both sides of the bin count where few bins take the vector kernel (384), with
+    1 to 4 waves per workgroup, against the oracle; pool rows past the lengths hold NaN."""
+    _gpu()
+    ctx = [1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 80, 81, 128, 129, 700, 1601]
+    g = Geometry(1, 2, 2 * gqa, d, 16, 2)
+    wl = custom(8300 + gqa, g, len(ctx), dtype, ctx, budget=np.ones((1, 2)), jitter=0.0, kv_scale=0.5)
+    s = _small_session(wl, mode=mode, n_bins=n_bins, split_target=900)
+    compare_layer(s, 0, what=f"{dtype} d{d} gqa{gqa} mode {mode} bins {n_bins}")
+
+
 @pytest.mark.parametrize("dtype,d,gqa", [("bf16", 128, 8), ("bf16", 64, 3), ("f32", 128, 1), ("f32", 64, 5)])
 @pytest.mark.parametrize("pieces", [10, 11, 15, 16, 17, 63, 64, 65, 190])
 def test_merge_chain_edges(dtype, d, gqa, pieces):

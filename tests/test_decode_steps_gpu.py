@@ -187,6 +187,32 @@ def test_append_in_decode_is_bitwise_append_then_decode(geom, dtype, mode, merge
     assert int(sep.full.item()) == 0 and int(fus.full.item()) == 0
 
 
+@pytest.mark.parametrize("geom,dtype", [(Geometry(1, 4, 4, 64, 16, 2), "bf16"), (Geometry(1, 4, 16, 64, 16, 1), "bf16"),
+                                        (Geometry(1, 2, 18, 64, 16, 2), "bf16"), (Geometry(1, 4, 8, 64, 16, 2), "f32"),
+                                        (Geometry(1, 2, 10, 128, 16, 2), "f32")])
+def test_append_in_decode_on_the_matrix_kernels(geom, dtype):
+    """Plans of more bins than the vector kernel takes: the appended row lands in either page of a two-page step and
+    in every wave's page; bit for bit tg_append + tg_decode at each step, the last one against the oracle."""
+    _gpu()
+    B, T = 7, 35
+    wl, t, (sep, fus) = _twin_sessions(geom, B, dtype, (1, 900), tg.TG_PLAN_AOT_FILL, 909 + geom.num_q_heads, T, 400,
+                                       False)
+    rng = np.random.default_rng(37)
+    for step in range(1, T + 1):
+        _step_inputs(rng, sep, dtype)
+        for name in ("k_tok", "v_tok", "q"):
+            getattr(fus, name).copy_(getattr(sep, name))
+        sep.run_decode_step()
+        fus.run_decode_step()
+        torch.cuda.synchronize()
+        for name in ("out", "lse", "pool"):
+            assert _same_bits(getattr(sep, name), getattr(fus, name)), f"{name} differs at step {step}"
+        assert torch.equal(sep.live_len, fus.live_len), f"live lengths differ at step {step}"
+    O, _ = oracle.decode_attention(_f64(fus.q)[0], _f64(fus.pool), 0, geom=geom, batch=B, kv_len=t.kv_len + T,
+                                   offsets=t.pt_offsets, pages=t.pt_pages, group_of=t.group_of, slot_of=t.slot_of)
+    check_close(_f64(fus.out[0]).reshape(-1, geom.head_dim), O.reshape(-1, geom.head_dim), dtype, "last step")
+
+
 def test_append_in_decode_without_room_matches_append_launch():
     """Heads whose table is full take no token in either form: the flag is set, nothing is stored, and the
     attention runs over the full table; the other heads append (matrix-core and generic kernels)."""
