@@ -277,7 +277,10 @@ __global__ __launch_bounds__(kSelThreads) void tg_compress_select_kernel(SelectP
 
 // Copies the K and V rows of ranks [r0, r0 + rows) of one unit: rank j's
 // chunk index is tok(j); it goes to the head's entry cursor + j.  Called by a
-// whole workgroup, kUnroll rows in flight per thread.
+// whole workgroup, kUnroll rows in flight per thread.  Bound by HBM: the rows
+// go to pages that nothing reads again soon, so the stores are non-temporal
+// and leave the L2 to the loads (16 requests, chunk 8192, 318 MB: 81.1 -> 73.7
+// us for the call, 4.3 TB/s; with non-temporal loads as well 78.1).
 template <int kUnroll, typename TokFn>
 __device__ __forceinline__ void copy_rows(const CopyParams& p, const tg_compress_item& it, int r0, int rows,
                                           TokFn tok, int tid = threadIdx.x, int nthreads = kThreads) {
@@ -310,8 +313,8 @@ __device__ __forceinline__ void copy_rows(const CopyParams& p, const tg_compress
         const int pos = it.cursor + r0 + j;
         const int row = p.p_shift >= 0 ? pos & (p.P - 1) : pos % p.P;
         const int64_t dst = (((int64_t)page[u] * 2 * p.Hp + it.slot) * p.P + row) * lpr + sub;
-        p.pool[dst] = kk[u];
-        p.pool[dst + v_plane] = vv[u];
+        __builtin_nontemporal_store(kk[u], p.pool + dst);
+        __builtin_nontemporal_store(vv[u], p.pool + dst + v_plane);
       }
     }
   }
