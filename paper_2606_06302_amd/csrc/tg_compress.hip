@@ -7,13 +7,13 @@
 // ranks (tg_compress_wave_kernel).  Longer chunks take two launches on the
 // caller's stream:
 //   select - one workgroup per (request, KV head) unit, 512 threads up to
-//     4096 chunk entries and 1024 above (8 to 16 keys per thread):
-//     1. the unit's n scores become order-preserving 32-bit keys in LDS
+//     4096 chunk entries and 1024 above (4 to 16 keys per thread):
+//     1. the unit's n scores become order-preserving 32-bit keys in registers
 //        (larger score = larger key; -0 maps to +0; NaN maps to 0, below all);
-//     2. a most-significant-digit-first radix select (up to four 8-bit
-//        passes, one LDS histogram per wave) finds the count-th largest key T
-//        and how many entries equal to T are kept (the lowest-index ones); it
-//        stops early once the chosen digit's whole bucket is kept;
+//     2. a most-significant-digit-first radix select (up to three passes of 11,
+//        11 and 10 bits) finds the count-th largest key T and how many entries
+//        equal to T are kept (the lowest-index ones); it stops early once the
+//        chosen digit's whole bucket is kept;
 //     3. each wave walks its share of the tokens 64 at a time; ballots of
 //        the "kept" and "equal to T" predicates and lane-prefix bit counts
 //        give every kept entry its rank in token order, written to kept[].
@@ -28,10 +28,8 @@
 namespace {
 
 constexpr int kThreads = 256;           // copy launch
-constexpr int kBins = 256;              // one radix digit of 8 bits
+constexpr int kBins = 256;              // one radix digit of 8 bits (short chunks)
 constexpr int kUnroll = 4;           // rows in flight per thread in the copy launch
-constexpr int kBatch = 8;            // score loads / LDS key reads in flight per thread
-constexpr int kGroups = 4;           // 64-token groups per batch of the ranking walk
 constexpr int kFusedMaxChunk = TG_COMPRESS_ONE_LAUNCH_MAX_CHUNK; // chunks up to this many tokens are compressed in one launch
 
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
@@ -105,174 +103,129 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Top(count) of one unit's chunk scores: the kept chunk indices in ascending
-// order go to kept[].  Called by a whole workgroup of kSelThreads threads; keys
-// is LDS room for C keys.
-template <int kSelThreads>
-__device__ __forceinline__ void select_unit(const SelectParams& p, int64_t unit, uint32_t* keys) {
+// Select launch: Top(count) of one unit's chunk scores, one workgroup of
+// kSelThreads threads per unit; the kept chunk indices in ascending order go to
+// kept[].  Every thread holds KPT keys in registers (wave w, slot i, lane l:
+// token 64 (KPT w + i) + l, so loads are coalesced and slot order is token
+// order within a wave).
+//
+// Bound by its chain of steps, not by bytes.  The radix digits are 11 bits (the
+// last 10) in one histogram for the whole workgroup: the top digit then holds
+// the exponent and two bits of the mantissa, so the lanes of a wave seldom meet
+// on a counter, and two passes usually find the threshold.  16 requests of 8
+// heads, against 8-bit digits per wave and keys in LDS: chunk 2048 5.4 / 7.2 us,
+// 4096 6.9 / 9.7, 8192 9.0 / 15.1, 16384 16.2 / 23.8.
+template <int kSelThreads, int KPT>
+__global__ __launch_bounds__(kSelThreads) void tg_compress_select_kernel(SelectParams p) {
   constexpr int kWaves = kSelThreads / 64;
-  // per-wave digit histograms, two buffers: a pass reads one while the
-  // waves build the next pass's in the other, each wave clearing its own
-  __shared__ __align__(16) uint32_t hist[2][kWaves][kBins];
+  constexpr int kDigits = 2048;
+  constexpr int kPer = kDigits / kSelThreads;   // counters per thread in the digit search
+  __shared__ __align__(16) uint32_t hist[2][kDigits];
+  __shared__ int32_t wave_sum[kWaves];
+  __shared__ int32_t found[3];                  // digit, how many of its bucket are kept, whether all are
   __shared__ int32_t wave_cnt[2][kWaves];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t unit = blockIdx.x;
   const int b = (int)(unit / p.H);
-  // the first batch of scores is requested before the counts arrive: it
-  // covers chunk entries that exist whatever chunk_tokens says
+  // the scores are requested before the counts arrive: entries below C exist
+  // whatever chunk_tokens says
   const uint32_t* sc = p.scores + unit * p.C;
-  uint32_t v[kBatch];
+  const int t0 = wave * (KPT * 64) + lane;
+  uint32_t key[KPT];
 #pragma unroll
-  for (int u = 0; u < kBatch; ++u) {
-    const int t = tid + u * kSelThreads;
-    v[u] = t < p.C ? sc[t] : 0u;
-  }
+  for (int i = 0; i < KPT; ++i) key[i] = t0 + 64 * i < p.C ? sc[t0 + 64 * i] : 0u;
+  for (int j = tid; j < 2 * kDigits / 4; j += kSelThreads) reinterpret_cast<u4*>(&hist[0][0])[j] = u4(0u);
   const int n = min(max(((const TG_CONST int32_t*)p.chunk_tokens)[b], 0), p.C);
   const int count = min(max(((const TG_CONST int32_t*)p.keep_count)[unit], 0), n);
   if (count == 0) return;                        // the whole workgroup leaves together
   const bool keep_all = count >= n;
-
-  if (!keep_all) *reinterpret_cast<u4*>(&hist[0][wave][4 * lane]) = u4(0u);
-  // keys into LDS, kBatch loads in flight per thread; the histogram of the
-  // top digit is taken on the way
-  for (int t0 = tid; t0 < n; t0 += kBatch * kSelThreads) {
-    if (t0 != tid) {
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const int t = t0 + u * kSelThreads;
-        v[u] = t < n ? sc[t] : 0u;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int t = t0 + u * kSelThreads;
-      if (t < n) {
-        const uint32_t key = order_key(v[u]);
-        keys[t] = key;
-        if (!keep_all) atomicAdd(&hist[0][wave][key >> 24], 1u);
-      }
-    }
-  }
-  __syncthreads();   // keys and the first histogram complete
+  for (int i = 0; i < KPT; ++i) key[i] = order_key(key[i]);
+  __syncthreads();                               // histograms clear
 
   // radix select over the digits from the top: after each pass, thr holds the
   // digits of the count-th largest key found so far (mask marks them) and
   // need = how many keys with that prefix are kept.  When the whole bucket of
   // the chosen prefix is kept (need == its size), the lower digits cannot
   // change the kept set and the walk stops: the kept keys are then those whose
-  // prefix is larger than thr's, or equal to it.  Every wave finds the digit
-  // itself, so a pass costs one barrier (after its histogram).
+  // prefix is larger than thr's, or equal to it.
   uint32_t thr = 0, mask = 0;
   int need = count;
   if (!keep_all) {
     int buf = 0;
-    for (int shift = 24;; shift -= 8) {
-      // lane i owns digits 255-4i .. 252-4i, in descending order
-      int c[4] = {0, 0, 0, 0};
+    for (int shift = 21;;) {
+      const uint32_t dmask = shift > 0 ? 2047u : 1023u;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
-        const u4 h = *reinterpret_cast<const u4*>(&hist[buf][w][252 - 4 * lane]);
-        c[0] += (int)h.w;
-        c[1] += (int)h.z;
-        c[2] += (int)h.y;
-        c[3] += (int)h.x;
+      for (int i = 0; i < KPT; ++i)
+        if (t0 + 64 * i < n && (key[i] & mask) == thr) atomicAdd(&hist[buf][(key[i] >> shift) & dmask], 1u);
+      __syncthreads();
+      // thread i owns kPer counters, both in descending order of digit
+      int c[kPer], s = 0;
+      const int top = kDigits - 1 - kPer * tid;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        c[j] = (int)hist[buf][top - j];
+        s += c[j];
       }
-      const int s = c[0] + c[1] + c[2] + c[3];
-      int run = wave_inclusive_sum(s) - s;   // matching keys with a larger digit
-      int f_digit = -1, f_need = 0, f_whole = 0;
+      const int in_wave = wave_inclusive_sum(s);
+      if (lane == 63) wave_sum[wave] = in_wave;
+      __syncthreads();
+      const int ws = lane < kWaves ? wave_sum[lane] : 0;
+      int run = __builtin_amdgcn_readlane(wave_inclusive_sum(ws) - ws, wave) + in_wave - s;   // keys with a larger digit
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (run < need && run + c[j] >= need) {
-          f_digit = 255 - 4 * lane - j;
-          f_need = need - run;
-          f_whole = run + c[j] == need;       // the bucket is kept whole
+      for (int j = 0; j < kPer; ++j) {
+        if (run < need && run + c[j] >= need) {   // exactly one thread: the count-th largest matching key exists
+          found[0] = top - j;
+          found[1] = need - run;
+          found[2] = run + c[j] == need;
         }
         run += c[j];
       }
-      // exactly one lane holds the digit: the count-th largest matching key exists
-      const uint64_t holder = __ballot(f_digit >= 0);
-      const int src = holder ? (int)__builtin_ctzll(holder) : 0;
-      const int digit = __builtin_amdgcn_readlane(f_digit, src);
-      need = __builtin_amdgcn_readlane(f_need, src);
-      thr |= (uint32_t)digit << shift;
-      mask |= 0xffu << shift;
-      if (__builtin_amdgcn_readlane(f_whole, src) || shift == 0) break;
-      // the next digit's histogram over the keys that share the prefix
-      buf ^= 1;
-      *reinterpret_cast<u4*>(&hist[buf][wave][4 * lane]) = u4(0u);
-      for (int t0 = tid; t0 < n; t0 += kBatch * kSelThreads) {
-        uint32_t kk[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-          const int t = t0 + u * kSelThreads;
-          kk[u] = t < n ? keys[t] : ~thr;    // ~thr never matches thr under mask (mask != 0 here)
-        }
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u)
-          if ((kk[u] & mask) == thr) atomicAdd(&hist[buf][wave][(kk[u] >> (shift - 8)) & 0xffu], 1u);
-      }
       __syncthreads();
+      thr |= (uint32_t)__builtin_amdgcn_readfirstlane(found[0]) << shift;
+      mask |= dmask << shift;
+      need = __builtin_amdgcn_readfirstlane(found[1]);
+      if (__builtin_amdgcn_readfirstlane(found[2]) || shift == 0) break;
+      // every thread is past its reads of this buffer: clear it for the pass after the next
+      for (int j = tid; j < kDigits / 4; j += kSelThreads) reinterpret_cast<u4*>(&hist[buf][0])[j] = u4(0u);
+      buf ^= 1;
+      shift = shift == 21 ? 10 : 0;
     }
   }
 
-  // ranks in token order: wave w owns tokens [w*span, (w+1)*span), walked in
-  // groups of 64, kGroups groups per batch of LDS reads
-  const int span = ((n + kSelThreads - 1) / kSelThreads) * 64;
-  const int t_begin = wave * span, t_end = min(n, t_begin + span);
+  // ranks in token order: every wave counts its share, then walks it slot by slot
   int gt_w = 0, eq_w = 0;
-  for (int base = t_begin; base < t_end; base += 64 * kGroups) {
-    uint32_t kk[kGroups];
 #pragma unroll
-    for (int u = 0; u < kGroups; ++u) {
-      const int t = base + 64 * u + lane;
-      kk[u] = t < t_end ? keys[t] & mask : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < kGroups; ++u) {
-      const bool valid = base + 64 * u + lane < t_end;
-      gt_w += __popcll(__ballot(valid && (keep_all || kk[u] > thr)));
-      eq_w += __popcll(__ballot(valid && !keep_all && kk[u] == thr));
-    }
+  for (int i = 0; i < KPT; ++i) {
+    const bool valid = t0 + 64 * i < n;
+    const uint32_t kk = key[i] & mask;
+    gt_w += __popcll(__ballot(valid && (keep_all || kk > thr)));
+    eq_w += __popcll(__ballot(valid && !keep_all && kk == thr));
   }
   if (lane == 0) {
     wave_cnt[0][wave] = gt_w;
     wave_cnt[1][wave] = eq_w;
   }
   __syncthreads();
-  int gt_before = 0, eq_before = 0;
-  for (int w = 0; w < wave; ++w) {
-    gt_before += wave_cnt[0][w];
-    eq_before += wave_cnt[1][w];
-  }
-  int run_eq = eq_before, run_kept = gt_before + min(eq_before, need);
+  const int cg = lane < kWaves ? wave_cnt[0][lane] : 0, ce = lane < kWaves ? wave_cnt[1][lane] : 0;
+  const int gt_before = __builtin_amdgcn_readlane(wave_inclusive_sum(cg) - cg, wave);
+  int run_eq = __builtin_amdgcn_readlane(wave_inclusive_sum(ce) - ce, wave);
+  int run_kept = gt_before + min(run_eq, need);
   int32_t* out = p.kept + unit * p.C;
-  for (int base = t_begin; base < t_end; base += 64 * kGroups) {
-    uint32_t kk[kGroups];
 #pragma unroll
-    for (int u = 0; u < kGroups; ++u) {
-      const int t = base + 64 * u + lane;
-      kk[u] = t < t_end ? keys[t] & mask : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < kGroups; ++u) {
-      const int t = base + 64 * u + lane;
-      const bool valid = t < t_end;
-      const bool eq = valid && !keep_all && kk[u] == thr;
-      const uint64_t eq_mask = __ballot(eq);
-      const bool keep = valid && (keep_all || kk[u] > thr || (eq && run_eq + lanes_below(eq_mask) < need));
-      const uint64_t keep_mask = __ballot(keep);
-      if (keep) out[run_kept + lanes_below(keep_mask)] = t;
-      run_eq += __popcll(eq_mask);
-      run_kept += __popcll(keep_mask);
-    }
+  for (int i = 0; i < KPT; ++i) {
+    const int t = t0 + 64 * i;
+    const bool valid = t < n;
+    const uint32_t kk = key[i] & mask;
+    const bool eq = valid && !keep_all && kk == thr;
+    const uint64_t eq_mask = __ballot(eq);
+    const bool keep = valid && (keep_all || kk > thr || (eq && run_eq + lanes_below(eq_mask) < need));
+    const uint64_t keep_mask = __ballot(keep);
+    if (keep) out[run_kept + lanes_below(keep_mask)] = t;
+    run_eq += __popcll(eq_mask);
+    run_kept += __popcll(keep_mask);
   }
-}
-
-// kSelThreads: 512 up to 4096 chunk entries, 1024 above (8 to 16 keys per thread)
-template <int kSelThreads>
-__global__ __launch_bounds__(kSelThreads) void tg_compress_select_kernel(SelectParams p) {
-  extern __shared__ uint32_t keys[];             // [C] keys of the unit's scores
-  select_unit<kSelThreads>(p, blockIdx.x, keys);
 }
 
 // Copies the K and V rows of ranks [r0, r0 + rows) of one unit: rank j's
@@ -332,7 +285,7 @@ __global__ __launch_bounds__(kThreads) void tg_compress_copy_kernel(CopyParams p
 // barrier: the wave holds its unit's whole chunk of keys in registers (lane
 // l, slot i: token 64*i + l, so the score loads are coalesced and token order
 // is slot-major), finds the count-th largest key with the same
-// most-significant-digit radix select as select_unit (the digit histogram in
+// most-significant-digit radix select as the select launch, on 8-bit digits (the histogram in
 // the wave's LDS, whose operations a wave executes in order), ranks the kept
 // entries by ballots in token order, and copies its own ranks.  The unit's
 // first item also writes kept[].  KPL = keys per lane.  Single-wave
@@ -487,18 +440,12 @@ extern "C" int32_t tg_compress(const tg_compress_args* a, void* hip_stream) {
     if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "compress launch failed: %s", hipGetErrorString(e));
     return TG_OK;
   }
-  const size_t lds = (size_t)a->chunk_len * sizeof(uint32_t);
-  const bool wide = a->chunk_len > 4096;
-  const void* select = wide ? reinterpret_cast<const void*>(tg_compress_select_kernel<1024>)
-                            : reinterpret_cast<const void*>(tg_compress_select_kernel<512>);
-  if (lds > 32768) {
-    hipError_t e = hipFuncSetAttribute(select, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "compress LDS attribute: %s", hipGetErrorString(e));
-  }
-  if (wide)
-    hipLaunchKernelGGL(tg_compress_select_kernel<1024>, dim3(a->batch * g.num_kv_heads), dim3(1024), lds, stream, s);
-  else
-    hipLaunchKernelGGL(tg_compress_select_kernel<512>, dim3(a->batch * g.num_kv_heads), dim3(512), lds, stream, s);
+  // 4 to 16 keys per thread: 512 threads up to 4096 entries, 1024 above
+  const dim3 units(a->batch * g.num_kv_heads);
+  if (a->chunk_len <= 2048) hipLaunchKernelGGL((tg_compress_select_kernel<512, 4>), units, dim3(512), 0, stream, s);
+  else if (a->chunk_len <= 4096) hipLaunchKernelGGL((tg_compress_select_kernel<512, 8>), units, dim3(512), 0, stream, s);
+  else if (a->chunk_len <= 8192) hipLaunchKernelGGL((tg_compress_select_kernel<1024, 8>), units, dim3(1024), 0, stream, s);
+  else hipLaunchKernelGGL((tg_compress_select_kernel<1024, 16>), units, dim3(1024), 0, stream, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "compress select launch failed: %s", hipGetErrorString(e));
   hipLaunchKernelGGL(tg_compress_copy_kernel, dim3(a->num_items), dim3(kThreads), 0, stream, c);

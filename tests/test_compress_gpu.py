@@ -117,6 +117,42 @@ def test_compress_chunk_lengths_at_kernel_boundaries(C):
     assert kept > 0
 
 
+@pytest.mark.parametrize("scores", ["special", "equal", "low_digit", "middle_digit"])
+@pytest.mark.parametrize("C", [1025, 2047, 2048, 2049, 8191, 8192, 8193, 16384])
+def test_select_launch_digit_and_size_edges(C, scores):
+    """The select launch at its keys-per-thread steps (2048, 4096, 8192 tokens), on scores that its first radix
+    digit (11 bits) decides, that only the last (10 bits) or the middle one decides, and that none does (all
+    equal): the kept lists equal a stable sort's, the rows kept are the chunk's."""
+    _gpu()
+    g = Geometry(1, 2, 4, 64, 16, 1)
+    B = 2
+    wl = custom(4300 + C, g, B, "bf16", C, chunk_len=C, budget=np.array([[0.37, 0.81]]), jitter=0.0)
+    rng = np.random.default_rng(C)
+    if scores == "special":
+        sc = host_scores(wl, (B, 2, C), special=True)
+    elif scores == "equal":
+        sc = np.full((B, 2, C), -1.25, dtype=np.float32)
+    else:
+        low = rng.integers(0, 1 << 10, size=(B, 2, C), dtype=np.uint32)
+        sc = (np.uint32(0x3F800000) + (low if scores == "low_digit" else low << np.uint32(10))).view(np.float32)
+    tables = Tables(wl)
+    pool = _pool_for(wl, tables)
+    toks = np.array([C, C - 5], dtype=np.int32)
+    s = CompressSession(wl, tables, pool, np.zeros(B, np.int32), toks, scores=torch.from_numpy(sc).cuda())
+    s.run()
+    torch.cuda.synchronize()
+    kept, count = s.kept.cpu().numpy(), s.plan["keep_count"]
+    for b in range(B):
+        for h in range(2):
+            n, c = int(toks[b]), int(count[b, h])
+            v = np.where(np.isnan(sc[b, h, :n]), -np.inf, sc[b, h, :n].astype(np.float64))
+            rank = np.lexsort((np.arange(n), -v, np.isnan(sc[b, h, :n])))   # NaN last, then by score, then by index
+            assert 0 < c < n and np.array_equal(kept[b, h, :c], np.sort(rank[:c])), (b, h)
+            page = int(tables.pt_pages[tables.pt_offsets[b * 2 + tables.group_of[0, h]] + (c - 1) // 16])
+            row = s.pool[page, 1, int(tables.slot_of[0, h]), (c - 1) % 16]
+            assert torch.equal(row, s.v_new[b, int(kept[b, h, c - 1]), h])
+
+
 def test_compress_three_chunks_then_decode():
     """A context compressed chunk by chunk fills its reservation exactly; decode attention over the
     resulting cache matches the oracle (prefill compression feeding the decode kernel)."""
