@@ -413,8 +413,8 @@ __global__ void __launch_bounds__(kBlock) tg_decode_kernel(DecodeParams p, const
 //   * O^T[16 dims][16 heads] += V^T P^T, one product per 16 dims: 16 tokens deep
 //     (v_mfma_f32_16x16x16_bf16) at head_dim 128, 32 deep (16x16x32, k index
 //     8rb+i = token 4rb+i of the first page, then of the second) at 64, there
-//     once with P rounded to bf16 and once with the rest, so that P counts to
-//     2^-17.  P^T is the S^T tile of the same lane rounded to bf16 (the
+//     once with P cut to bf16 and once with the rest, so that P counts to
+//     2^-16.  P^T is the S^T tile of the same lane rounded to bf16 (the
 //     result layout of the first product is the operand layout of the second),
 //     and V^T comes from LDS with ds_read_b64_tr_b16, whose 4x4 lane transpose
 //     turns row-major V rows into the 4-consecutive-token operand.
@@ -721,14 +721,18 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
       for (int mm = 0; mm < D / 16; ++mm) acc[mm] *= alpha;
     }
     const float mcs = m * cs;
-    s16x4 pb[KP], pl[KP];   // P rounded to bf16, and (head_dim 64) what the rounding left
+    s16x4 pb[KP], pl[KP];   // P as bf16, and (head_dim 64) what that left
 #pragma unroll
     for (int i = 0; i < 4 * KP; ++i) {
       const float pk = fast_exp2(fmaf(sv[i], cs, -mcs));
       l += pk;
-      const uint16_t hi = f32_to_bf16(pk);
-      pb[i / 4][i % 4] = (short)hi;
-      if constexpr (KP == 2) pl[i / 4][i % 4] = (short)f32_to_bf16(pk - __uint_as_float((uint32_t)hi << 16));
+      if constexpr (KP == 1) {
+        pb[i / 4][i % 4] = (short)f32_to_bf16(pk);
+      } else {   // cut, not rounded, and the rest kept above 0: both parts of p > 0 carry an infinite V on
+        const uint32_t hi = __float_as_uint(pk) & 0xffff0000u;
+        pb[i / 4][i % 4] = (short)(hi >> 16);
+        pl[i / 4][i % 4] = (short)f32_to_bf16(fmaf(pk, 0x1.000004p0f, -__uint_as_float(hi)));
+      }
     }
     // O^T += V^T P^T
     const bool partial = nvalid < kStep;

@@ -41,6 +41,36 @@ def _small_session(wl, mode=0, n_bins=None, split_target=None, free_seed=None, p
     return s
 
 
+@pytest.mark.parametrize("dtype,d,gqa,n_bins", [("bf16", 64, 8, 37), ("bf16", 64, 3, 700), ("bf16", 64, 3, 37),
+                                                ("f32", 64, 4, 37), ("f32", 128, 4, 37)])
+def test_infinite_values_stay_infinite(dtype, d, gqa, n_bins):
+    """An infinity in a retained V row whose weight is above 0 makes that output element infinite, with its sign, and
+    leaves the others alone: probabilities that enter the product in parts have no part that is 0 or negative."""
+    _gpu()
+    g = Geometry(1, 2, 2 * gqa, d, 16, 2)
+    wl = custom(61, g, 2, dtype, (50, 400), kv_scale=0.5)
+    say(f"infinite V: {dtype} d={d} gqa={gqa} n_bins={n_bins}")
+    tables = Tables(wl)
+    host = poisoned_host_pool(wl, tables)
+    clean = torch.from_numpy(host).to({"f32": torch.float32, "bf16": torch.bfloat16}[dtype]).cuda()
+    pool = clean.clone()
+    page = lambda b, h, e: int(tables.pt_pages[int(tables.pt_offsets[b * g.num_groups + int(tables.group_of[0, h])]) + e // 16])
+    for b in range(2):
+        for h in range(2):
+            s, n = int(tables.slot_of[0, h]), int(tables.kv_len[b, 0, h])
+            for e, dim, v in ((0, 1, np.inf), (n // 2, d // 2, -np.inf), (n - 1, d - 1, np.inf)):
+                pool[page(b, h, e), 1, s, e % 16, dim] = v
+    outs = []
+    for x in (clean, pool):
+        ds = DecodeSession(wl, tables=tables, mode=tg.TG_PLAN_AOT_FILL, n_bins=n_bins, fill="host", pool=x)
+        ds.run_step()
+        torch.cuda.synchronize()
+        outs.append(ds.out[0].float())
+    want = outs[0].clone()
+    want[..., 1], want[..., d // 2], want[..., d - 1] = np.inf, -np.inf, np.inf
+    assert torch.equal(outs[1], want)
+
+
 @pytest.mark.parametrize("mode,n_bins,st", [(0, 8, 16), (0, 1, 1), (0, 512, 2048), (0, 3, 40), (1, None, None),
                                             (2, 64, None), (3, 8, None), (3, 300, None)])
 def test_config1_tiny_fp32_all_plans(mode, n_bins, st):
