@@ -230,11 +230,15 @@ __global__ __launch_bounds__(kSelThreads) void tg_compress_select_kernel(SelectP
 
 // Copies the K and V rows of ranks [r0, r0 + rows) of one unit: rank j's
 // chunk index is tok(j); it goes to the head's entry cursor + j.  Called by a
-// whole workgroup, kUnroll rows in flight per thread.  Bound by HBM: the rows
-// go to pages that nothing reads again soon, so the stores are non-temporal
-// and leave the L2 to the loads (16 requests, chunk 8192, 318 MB: 81.1 -> 73.7
-// us for the call, 4.3 TB/s; with non-temporal loads as well 78.1).
-template <int kUnroll, typename TokFn>
+// whole workgroup, kUnroll rows in flight per thread.  Bound by HBM.
+// kStream: non-temporal stores, which leave the L2 to the loads and nothing to
+// write back at the launch's end.  They pay in the one-wave form (16 requests,
+// chunk 512 8.4 -> 7.6 us, 1024 14.0 -> 13.2, 1024 f32 22.8 -> 20.6; first pass
+// over new buffers level).  Chunks of the two-launch form are larger than the
+// caches: at 8192 (290 MB) repeated passes took 68 instead of 76 us, because
+// the rows read last time stayed in the caches, but a first pass, what a chunk
+// is in use, 103 instead of 88: plain stores there.
+template <int kUnroll, bool kStream, typename TokFn>
 __device__ __forceinline__ void copy_rows(const CopyParams& p, const tg_compress_item& it, int r0, int rows,
                                           TokFn tok, int tid = threadIdx.x, int nthreads = kThreads) {
   const int lpr = p.row_u4;
@@ -266,8 +270,13 @@ __device__ __forceinline__ void copy_rows(const CopyParams& p, const tg_compress
         const int pos = it.cursor + r0 + j;
         const int row = p.p_shift >= 0 ? pos & (p.P - 1) : pos % p.P;
         const int64_t dst = (((int64_t)page[u] * 2 * p.Hp + it.slot) * p.P + row) * lpr + sub;
-        __builtin_nontemporal_store(kk[u], p.pool + dst);
-        __builtin_nontemporal_store(vv[u], p.pool + dst + v_plane);
+        if constexpr (kStream) {
+          __builtin_nontemporal_store(kk[u], p.pool + dst);
+          __builtin_nontemporal_store(vv[u], p.pool + dst + v_plane);
+        } else {
+          p.pool[dst] = kk[u];
+          p.pool[dst + v_plane] = vv[u];
+        }
       }
     }
   }
@@ -278,7 +287,7 @@ __global__ __launch_bounds__(kThreads) void tg_compress_copy_kernel(CopyParams p
   const int r0 = max(it.rank_begin, 0);
   const int r1 = min(min(it.rank_end, min(it.count, p.C)), r0 + TG_COMPRESS_MAX_ROWS);
   const int32_t* src_tok = p.kept + ((int64_t)it.b * p.H + it.kv_head) * p.C + r0;
-  copy_rows<kUnroll>(p, it, r0, r1 - r0, [&](int j) { return src_tok[j]; });
+  copy_rows<kUnroll, false>(p, it, r0, r1 - r0, [&](int j) { return src_tok[j]; });
 }
 
 // Short chunks in one launch, one single-wave workgroup per work item and no
@@ -381,7 +390,7 @@ __global__ __launch_bounds__(64) void tg_compress_wave_kernel(SelectParams sp, C
   }
   const int r0 = max(it.rank_begin, 0);
   const int r1 = min(min(it.rank_end, min(count, min(it.count, p.C))), r0 + TG_COMPRESS_MAX_ROWS);
-  copy_rows<8>(p, it, r0, r1 - r0, [&](int j) { return kl[r0 + j]; }, lane, 64);
+  copy_rows<8, true>(p, it, r0, r1 - r0, [&](int j) { return kl[r0 + j]; }, lane, 64);
   if (it.rank_begin == 0) {
     int32_t* out = sp.kept + unit * p.C;
     for (int r = lane; r < count; r += 64) out[r] = kl[r];
