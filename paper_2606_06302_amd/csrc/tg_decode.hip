@@ -6,8 +6,8 @@
 // (tg_build_plan, Algorithm 1's proportional rule or the sequential fill)
 // cuts every (b, h) into page-aligned chunks and places them on n_bins bins;
 // worker k of the launch runs bin k (a wave in the bf16 matrix-core kernel, a
-// workgroup in the fp32 one and in the vector kernel, which few bins take).  A chunk of a split unit writes an fp32
-// partial (o, lse), and the partials of every split unit are combined with a
+// workgroup in the fp32 one and in the vector kernel, which few query heads and
+// few bins take).  A chunk of a split unit writes an fp32 partial (o, lse), and the partials of every split unit are combined with a
 // log-sum-exp merge (split-KV decoding, Section 2.2.3): by tg_merge_kernel,
 // launched right after on the same stream, or, with arrival counters, inside
 // the head_dim-128 bf16 launch by the piece that finishes last.  The in-launch merge
@@ -205,9 +205,9 @@ __device__ __forceinline__ void finish_item(const DecodeParams& p, const tg_work
 }
 
 // ---------------------------------------------------------------------------
-// Vector kernel for few bins and few query heads (vector_kernel_pays() below):
-// the 4 waves of a workgroup share a bin, and with 1 to 4 query heads per KV
-// head the vector ALU keeps up with them.  A page slab (P=16 rows of one head, d*sizeof(T) bytes each) is read
+// Vector kernel for few query heads and for few bins (vector_kernel_pays()
+// below): the 4 waves of a workgroup share a bin, and with 1 to 4 query heads
+// per KV head the vector ALU keeps up with them.  A page slab (P=16 rows of one head, d*sizeof(T) bytes each) is read
 // with one 16-byte load per lane per 64 chunks; lane l owns chunk l % CPR of
 // token row l / CPR (CPR = 16-byte chunks per row).  q.k uses v_dot2_f32_bf16
 // on raw bf16 pairs (fp32 FMAs for fp32 data) and a DPP all-reduce over the CPR
@@ -968,6 +968,11 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
 // Bound by HBM; the 64 products of a page at head_dim 128 take about 1 us of
 // the 5 a page is given then.  16 requests, gqa 4, 223 MB: 41 us, 5.4 TB/s,
 // against 50 on the vector kernel; gqa 16, 134 MB: 97 -> 36 us with the merge.
+// The non-temporal loads pay past the 256 MB the caches hold (gqa 4, 582 MB: 104
+// us, plain 112; 792 MB at head_dim 64: 132, plain 145) and cost repeated
+// passes over less (198 MB: 42, plain 38; after the caches were replaced both
+// 45).  Loading an item's queries while the item before runs, into a second
+// buffer, measured slower at 64 (14.2 -> 15.8 us at 31 MB) and level at 128.
 template <int D>
 __global__ void __launch_bounds__(kBlock, 2) tg_decode_f32_kernel(DecodeParams p, const tg_work_item* __restrict__ items_g,
                                                                  const int32_t* __restrict__ pt_g,
@@ -1381,26 +1386,41 @@ using DecodeFn = void (*)(DecodeParams, const tg_work_item*, const int32_t*, con
 
 constexpr int kMaxGqa = 16;
 
-// Where the vector kernel is the faster one: plans of few bins (one worker per
-// unit, say), whose time is that of one worker.  There four waves on a bin, and
-// at few query heads no 16-column matrix tiles, win.  Measured at 128 bins of
-// one unit each (16 requests, 8192 tokens), vector against matrix kernel: bf16
-// head_dim 64, gqa 1 / 4 71 / 133 against 204 / 204 us, gqa 8 (64 bins) 194
-// against 189; f32 gqa 1 107 against 128 (64) and 155 against 214 us (128),
-// gqa 4 194 against 128 and 301 against 213.  At 256 bins of equal shares:
-// bf16 gqa 1 / 4 20 / 31 against 36 / 37 us; at 1024 the matrix kernels win
-// (bf16 23 / 26 against 18 / 19 us).
+// Where the vector kernel runs.  With few query heads the matrix kernels' 16
+// columns stay mostly empty and their few, large workgroups wait longer for
+// each item's queries, barriers and rounds than the vector kernel's many small
+// ones; there it runs at any number of bins, each plan at the bins its own
+// occupancy gives (8 KV heads, vector against matrix kernel, repeated passes /
+// after the caches were replaced, us):
+//   f32 gqa 1, 64 requests of 200 to 1000 tokens: head_dim 64 17 / 22 against
+//     21 / 26, 128 23 / 29 against 31 / 36; gqa 3 19 / 24 against 21 / 26 and
+//     29 / 36 against 32 / 38; 12 of 2000 to 8000 tokens, 128: gqa 1 35 / 44
+//     against 42 / 45, gqa 3 39 / 48 against 42 / 45.  At gqa 4 the matrix
+//     kernel is ahead or level everywhere (32 / 38 against 31 / 37, 42 / 51
+//     against 42 / 45).  Past the 256 MB the caches hold, it is ahead by 6 to
+//     10 % at any gqa (582 MB, gqa 1: 110 against 103), which a plan does not
+//     show on the host.
+//   bf16 head_dim 64, gqa 1: 64 requests of 200 to 1000 tokens 13.1 against 14.0
+//     (19 against 19), 32 of 300 to 3000 11.6 against 15.0 (17 against 20);
+//     396 MB 81 against 70.
+// Plans of few bins (one worker per unit, say) are bound by one worker, and
+// four waves on a bin win at up to four heads: 128 bins of one unit each (16
+// requests, 8192 tokens), bf16 head_dim 64, gqa 4 133 against 204 us, gqa 8 (64
+// bins) 194 against 189; 256 bins of equal shares gqa 4 31 against 37, at 1024
+// 26 against 19.
 bool vector_kernel_pays(int dtype, int d, int gqa, int n_bins) {
-  if (n_bins > 384) return false;
-  return dtype == TG_F32 ? gqa <= 2 : d == 64 && gqa <= 4;
+  if (dtype == TG_F32) return gqa <= 3;
+  return d == 64 && (gqa == 1 || (gqa <= 4 && n_bins <= 384));
 }
 
 template <typename T, int D>
 DecodeFn pick_vector(int gqa) {
-  if constexpr (sizeof(T) == 4) return gqa == 1 ? &tg_decode_kernel<T, D, 1> : &tg_decode_kernel<T, D, 2>;
-  else
-    return gqa == 1 ? &tg_decode_kernel<T, D, 1>
-                    : gqa == 2 ? &tg_decode_kernel<T, D, 2> : gqa == 3 ? &tg_decode_kernel<T, D, 3> : &tg_decode_kernel<T, D, 4>;
+  if (gqa == 1) return &tg_decode_kernel<T, D, 1>;
+  if (gqa == 2) return &tg_decode_kernel<T, D, 2>;
+  if constexpr (sizeof(T) == 2) {
+    if (gqa == 4) return &tg_decode_kernel<T, D, 4>;
+  }
+  return &tg_decode_kernel<T, D, 3>;
 }
 
 DecodeFn pick_decode(int dtype, int d, int gqa, int n_bins) {
@@ -1414,6 +1434,11 @@ DecodeFn pick_decode(int dtype, int d, int gqa, int n_bins) {
   if (dtype == TG_F32 && d == 64) return &tg_decode_f32_kernel<64>;
   if (dtype == TG_F32 && d == 128) return &tg_decode_f32_kernel<128>;
   return nullptr;
+}
+
+// whether every wave runs a bin of its own (the bf16 matrix kernel)
+bool wave_per_bin(int dtype, int d, int gqa, int n_bins) {
+  return dtype == TG_BF16 && !vector_kernel_pays(dtype, d, gqa, n_bins);
 }
 
 // Waves per workgroup of the bf16 kernel, each with a bin of its own.  Its LDS
@@ -1536,7 +1561,7 @@ int32_t decode_impl(const tg_decode_args* a, void* ws_ptr, size_t ws_bytes, void
   if (a->num_items == 0) return TG_OK;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   DecodeFn fn = pick_decode(a->dtype, g.head_dim, gqa, a->n_bins);
-  const bool wave_bins = a->dtype == TG_BF16 && !vector_kernel_pays(a->dtype, g.head_dim, gqa, a->n_bins);
+  const bool wave_bins = wave_per_bin(a->dtype, g.head_dim, gqa, a->n_bins);
   const int waves = wave_bins ? waves_per_wg(a->n_bins) : kWaves;
   const int bins = wave_bins ? waves : 1;   // bins per workgroup
   hipLaunchKernelGGL(fn, dim3((a->n_bins + bins - 1) / bins), dim3(64 * waves), 0, st, p, a->items, a->pt_pages,
@@ -1574,7 +1599,9 @@ size_t tg_decode_workspace_bytes(const tg_geometry* geom, int32_t batch, int32_t
 int32_t tg_decode_max_ctas(const tg_geometry* geom, int32_t dtype, int32_t device, int32_t* n_cta) {
   if (!n_cta) return tg::fail(TG_ERR_INVALID_ARG, "n_cta is NULL");
   if (int32_t rc = check_decode_shape(geom, dtype)) return rc;
-  DecodeFn fn = pick_decode(dtype, geom->head_dim, geom->num_q_heads / geom->num_kv_heads, INT32_MAX);
+  // the kernel that a plan of as many bins as fit runs on
+  const int gqa = geom->num_q_heads / geom->num_kv_heads;
+  DecodeFn fn = pick_decode(dtype, geom->head_dim, gqa, INT32_MAX);
   int cus = 0, per_cu = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
     return tg::fail(TG_ERR_HIP, "hipDeviceGetAttribute failed for device %d", device);
@@ -1584,7 +1611,7 @@ int32_t tg_decode_max_ctas(const tg_geometry* geom, int32_t dtype, int32_t devic
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), kBlock, 0);
   if (prev != device) (void)hipSetDevice(prev);
   if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "occupancy query failed: %s", hipGetErrorString(e));
-  *n_cta = per_cu * cus * (dtype == TG_BF16 ? kWaves : 1);
+  *n_cta = per_cu * cus * (wave_per_bin(dtype, geom->head_dim, gqa, INT32_MAX) ? kWaves : 1);
   return TG_OK;
 }
 

@@ -355,14 +355,28 @@ def test_fused_merge_matches_two_launch_merge_bitwise(gqa, mode, n_bins, st):
         compare_layer(fused, l, what=f"fused merge layer {l}")
 
 
+@pytest.mark.parametrize("dtype,d,gqa,per_cu", [("f32", 64, 1, 6), ("f32", 64, 2, 5), ("f32", 64, 3, 4),
+                                                ("f32", 128, 1, 4), ("f32", 128, 2, 4), ("f32", 128, 3, 3),
+                                                ("bf16", 64, 1, 6)])
+def test_default_bins_fit_the_vector_kernel(dtype, d, gqa, per_cu):
+    """With few query heads a session's default plan runs on the vector kernel, with as many bins as that kernel's
+    workgroups fit the chip (one bin each), more than the matrix kernels' workgroups would."""
+    _gpu()
+    g = Geometry(1, 2, 2 * gqa, d, 16, 2)
+    s = _small_session(custom(8200 + gqa, g, 2, dtype, (100, 3000), kv_scale=0.5), mode=tg.TG_PLAN_AOT_FILL)
+    assert s.n_bins >= per_cu * torch.cuda.get_device_properties(0).multi_processor_count
+    assert s.workers_per_wg() == 1
+    compare_layer(s, 0, what=f"{dtype} d{d} gqa{gqa} default bins")
+
+
 @pytest.mark.parametrize("dtype,d,gqa", [("bf16", 64, 1), ("bf16", 64, 4), ("bf16", 64, 8), ("bf16", 64, 9),
                                          ("bf16", 64, 16), ("f32", 64, 2), ("f32", 64, 5), ("f32", 64, 16),
                                          ("f32", 128, 1), ("f32", 128, 7), ("f32", 128, 16), ("bf16", 128, 8)])
 @pytest.mark.parametrize("mode,n_bins", [(3, 384), (3, 385), (3, 700), (3, 1025), (0, 500), (1, None)])
 def test_kernel_choice_edges(dtype, d, gqa, mode, n_bins):
     """Units around one and two 16-token pages (the matrix kernels' tiles, and the two-page steps of bf16 head_dim
-    64) and around 4 waves' pages, on both sides of the bin count where few bins take the vector kernel (384), with
-    1 to 4 waves per workgroup, against the oracle; pool rows past the lengths hold NaN."""
+    64) and around 4 waves' pages, on both sides of the bin count where few bins take the vector kernel (384; bf16
+    head_dim 64), with 1 to 4 waves per workgroup and at the default bins, against the oracle; pool rows past the lengths hold NaN."""
     _gpu()
     ctx = [1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 80, 81, 128, 129, 700, 1601]
     g = Geometry(1, 2, 2 * gqa, d, 16, 2)
