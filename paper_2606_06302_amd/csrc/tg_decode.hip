@@ -983,6 +983,7 @@ __global__ void __launch_bounds__(kBlock, 2) tg_decode_f32_kernel(DecodeParams p
   constexpr int kSlab = kPage * CPR;     // chunks per K or V slab of a page
   constexpr int NC = D / 16;             // 16-dim groups of q.k
   constexpr int NM = D / 64;             // 64-dim groups of p.v
+  constexpr int kAcc = D == 64 ? 4 : 2;  // accumulators a wave's tokens are dealt to
   constexpr float kSlack = 8.0f;
 
   __shared__ f32x4 sm_acc[kWaves][16][CPR + 1];   // padded: the rows of different heads on different banks
@@ -1082,9 +1083,14 @@ __global__ void __launch_bounds__(kBlock, 2) tg_decode_f32_kernel(DecodeParams p
     }
     const f32x4* const qv = &sm_q[hq][rb];
     float m = -INFINITY, l = 0.f;
-    f32x4 acc[2][NM][4];   // even and odd tokens, added at the item's end: half the rounding steps in a row
+    // added at the item's end, for short chains of roundings: as many as the
+    // vector kernel has, 16 in a workgroup at head_dim 64 and 8 at 128, where
+    // four a wave would not fit the registers.  With two at 64, long units were
+    // up to 1.13 times further from 64 bits than there; now 0.98 over the range
+    // (1.05 at most), for 0.3 us of 13 in short batches, none in long ones
+    f32x4 acc[kAcc][NM][4];
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
+    for (int e = 0; e < kAcc; ++e)
 #pragma unroll
       for (int mm = 0; mm < NM; ++mm)
 #pragma unroll
@@ -1128,18 +1134,15 @@ __global__ void __launch_bounds__(kBlock, 2) tg_decode_f32_kernel(DecodeParams p
 #pragma unroll
         for (int mm = 0; mm < NM; ++mm)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            acc[0][mm][j] *= alpha;
-            acc[1][mm][j] *= alpha;
-          }
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e = 0; e < kAcc; ++e) acc[e][mm][j] *= alpha;
       }
       // relative to m itself, not to a rounded m * cs: the state's m is what
       // the waves' and the pieces' states are weighted by
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        sv[i] = fast_exp2((sv[i] - m) * cs);
-        l += sv[i];
-      }
+      for (int i = 0; i < 4; ++i) sv[i] = fast_exp2((sv[i] - m) * cs);
+      l += (sv[0] + sv[1]) + (sv[2] + sv[3]);   // one rounding step a page in the long sum
       // O^T += V^T P^T
       const bool partial = nvalid < kPage;
 #pragma unroll
@@ -1152,7 +1155,8 @@ __global__ void __launch_bounds__(kBlock, 2) tg_decode_f32_kernel(DecodeParams p
         for (int mm = 0; mm < NM; ++mm)
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            acc[i & 1][mm][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[i][mm][j], sv[i], acc[i & 1][mm][j], 0, 0, 0);
+            acc[i % kAcc][mm][j] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(vc[i][mm][j], sv[i], acc[i % kAcc][mm][j], 0, 0, 0);
       }
       load_v(d, d_id);
       advance(d);
@@ -1164,12 +1168,20 @@ __global__ void __launch_bounds__(kBlock, 2) tg_decode_f32_kernel(DecodeParams p
     l = swap32_sum(swap16_sum(l));
     if (col < G) {
 #pragma unroll
-      for (int mm = 0; mm < NM; ++mm)
+      for (int mm = 0; mm < NM; ++mm) {
+        if constexpr (kAcc == 4) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            acc[0][mm][j] += acc[2][mm][j];
+            acc[1][mm][j] += acc[3][mm][j];
+          }
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           sm_acc[wave][col][16 * mm + 4 * rb + r] =
               f32x4{acc[0][mm][0][r] + acc[1][mm][0][r], acc[0][mm][1][r] + acc[1][mm][1][r],
                     acc[0][mm][2][r] + acc[1][mm][2][r], acc[0][mm][3][r] + acc[1][mm][3][r]};
+      }
       if (rb == 0) {
         sm_m[wave][col] = m;
         sm_l[wave][col] = l;

@@ -369,6 +369,36 @@ def test_default_bins_fit_the_vector_kernel(dtype, d, gqa, per_cu):
     compare_layer(s, 0, what=f"{dtype} d{d} gqa{gqa} default bins")
 
 
+@pytest.mark.parametrize("d,gqa,chains", [(64, 4, 16), (64, 16, 16), (128, 4, 8), (128, 16, 8)])
+def test_fp32_sums_keep_short_chains(d, gqa, chains):
+    """One long unit per bin with equal scores: the output is the mean of V, and its error against 64 bits is at most
+    that of fp32 sums in as many chains as the 4 waves' 16-byte row loads have rows in flight (4 x 4 rows at
+    head_dim 64, 4 x 2 at 128).  All terms are positive, so half the chains mean about 1.4 times the error; 1.2
+    leaves room for the scatter of 2 x d means."""
+    _gpu()
+    n = 16384
+    g = Geometry(1, 2, 2 * gqa, d, 16, 2)
+    wl = custom(8400 + gqa, g, 1, "f32", n, budget=np.ones((1, 2)), jitter=0.0)
+    tables = Tables(wl)
+    v = np.random.default_rng(d + gqa).uniform(1.0, 2.0, (2, n, d)).astype(np.float32)
+    pool = torch.zeros(tables.pool_pages, 2, 2, 16, d)
+    base = int(tables.pt_offsets[0])
+    for h in range(2):
+        ids = torch.from_numpy(tables.pt_pages[base: base + n // 16].astype(np.int64))
+        pool[ids, 1, int(tables.slot_of[0, h])] = torch.from_numpy(v[h].reshape(n // 16, 16, d))
+    s = DecodeSession(wl, tables=tables, mode=tg.TG_PLAN_AOT_FILL, n_bins=2, pool=pool.cuda(),
+                      q=torch.zeros(1, 1, 2 * gqa, d, device="cuda"))
+    s.run_step()
+    torch.cuda.synchronize()
+    exact = v.astype(np.float64).mean(1)
+    err = lambda x: float(np.sqrt((((x - exact) / exact) ** 2).mean()))
+    got = err(s.out[0, 0].double().cpu().numpy().reshape(2, gqa, d)[:, 0])
+    sums = np.add.accumulate(v.reshape(2, n // chains, chains, d), axis=1)[:, -1]
+    want = err(sums.astype(np.float64).sum(1) / n)
+    say(f"fp32 sums d={d} gqa={gqa}: {got:.3e}, in {chains} chains {want:.3e}")
+    assert s.plans[0]["num_partials"] == 0 and got <= 1.2 * want
+
+
 @pytest.mark.parametrize("dtype,d,gqa", [("bf16", 64, 1), ("bf16", 64, 4), ("bf16", 64, 8), ("bf16", 64, 9),
                                          ("bf16", 64, 16), ("f32", 64, 2), ("f32", 64, 5), ("f32", 64, 16),
                                          ("f32", 128, 1), ("f32", 128, 7), ("f32", 128, 16), ("bf16", 128, 8)])
