@@ -413,11 +413,13 @@ __global__ void __launch_bounds__(kBlock) tg_decode_kernel(DecodeParams p, const
 //   * O^T[16 dims][16 heads] += V^T P^T, one product per 16 dims: 16 tokens deep
 //     (v_mfma_f32_16x16x16_bf16) at head_dim 128, 32 deep (16x16x32, k index
 //     8rb+i = token 4rb+i of the first page, then of the second) at 64, there
-//     once with P cut to bf16 and once with the rest, so that P counts to
-//     2^-16.  P^T is the S^T tile of the same lane rounded to bf16 (the
-//     result layout of the first product is the operand layout of the second),
-//     and V^T comes from LDS with ds_read_b64_tr_b16, whose 4x4 lane transpose
-//     turns row-major V rows into the 4-consecutive-token operand.
+//     once for each of three bf16 parts of P, which hold its 24 bits (fp32
+//     partials are 5.9e-8 from 64 bits, 6.1e-8 on the vector kernel; with two
+//     parts 1.0e-6, at 1 to 5 % less time).  P^T is the S^T tile of the same
+//     lane (the result layout of the first product is the operand layout of the
+//     second; rounded to bf16 at head_dim 128), and V^T comes from LDS with
+//     ds_read_b64_tr_b16, whose 4x4 lane transpose turns row-major V rows into
+//     the 4-consecutive-token operand.
 //   * LDS layout: chunk c (16 bytes) of token row r sits at position c ^ k_swz(r)
 //     in the K slab and at c ^ v_swz(r) in the V slab (the DMA lanes pick their
 //     source chunk accordingly), so both operand reads are bank-conflict free:
@@ -665,7 +667,8 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
   tg_work_item item;
   u4 qv[D / 32];
   float m = -INFINITY, l = 0.f;
-  f32x4 acc[D / 16];
+  // acc2 (head_dim 64): what the lower parts of P add
+  f32x4 acc[D / 16], acc2[D / 16];
   for (;;) {
     if (pi == 0) {   // item start: its queries were DMA'd just before its first step
       item = load_item(items + it, p, &arow);
@@ -682,7 +685,7 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
       m = -INFINITY;
       l = 0.f;
 #pragma unroll
-      for (int mm = 0; mm < D / 16; ++mm) acc[mm] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int mm = 0; mm < D / 16; ++mm) acc[mm] = acc2[mm] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     if (d_live) {   // keep R-1 steps in flight: issue step k+R-1, then wait for step k
       issue(d, d_id, (k + R - 1) % R);
@@ -718,22 +721,36 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
       l *= alpha;
       m = m_new;
 #pragma unroll
-      for (int mm = 0; mm < D / 16; ++mm) acc[mm] *= alpha;
+      for (int mm = 0; mm < D / 16; ++mm) {
+        acc[mm] *= alpha;
+        if constexpr (KP == 2) acc2[mm] *= alpha;
+      }
     }
     const float mcs = m * cs;
-    s16x4 pb[KP], pl[KP];   // P as bf16, and (head_dim 64) what that left
+    s16x4 pb[KP], pm[KP], pl[KP];   // P as bf16, and (head_dim 64) the two parts that left
 #pragma unroll
     for (int i = 0; i < 4 * KP; ++i) {
       const float pk = fast_exp2(fmaf(sv[i], cs, -mcs));
-      l += pk;
       if constexpr (KP == 1) {
+        l += pk;
         pb[i / 4][i % 4] = (short)f32_to_bf16(pk);
-      } else {   // cut, not rounded, and the rest kept above 0: both parts of p > 0 carry an infinite V on
+      } else {
+        // three parts of 8 bits, cut and not rounded: their sum is p.  No part
+        // of a p > 0 is 0, so that none makes NaN of an infinite V: a part
+        // below the smallest normal number becomes that (p itself is 0 below
+        // it), an error of 2^-126 at most
+        const uint32_t tiny = __float_as_uint(fminf(pk, 0x1p-126f));
         const uint32_t hi = __float_as_uint(pk) & 0xffff0000u;
+        const float r1 = pk - __uint_as_float(hi);
+        const uint32_t mid = __float_as_uint(r1) & 0xffff0000u;
+        const uint32_t lo = __float_as_uint(r1 - __uint_as_float(mid));
         pb[i / 4][i % 4] = (short)(hi >> 16);
-        pl[i / 4][i % 4] = (short)f32_to_bf16(fmaf(pk, 0x1.000004p0f, -__uint_as_float(hi)));
+        pm[i / 4][i % 4] = (short)(max(mid, tiny) >> 16);   // as integers: the parts are not negative
+        pl[i / 4][i % 4] = (short)(max(lo, tiny) >> 16);
+        sv[i] = pk;
       }
     }
+    if constexpr (KP == 2) l += ((sv[0] + sv[1]) + (sv[2] + sv[3])) + ((sv[4] + sv[5]) + (sv[6] + sv[7]));
     // O^T += V^T P^T
     const bool partial = nvalid < kStep;
 #pragma unroll
@@ -753,7 +770,8 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
       } else {
         const u4 v = join(a[0], a[1]);
         acc[mm] = mfma_qk(v, join(pb[0], pb[1]), acc[mm]);
-        acc[mm] = mfma_qk(v, join(pl[0], pl[1]), acc[mm]);
+        acc2[mm] = mfma_qk(v, join(pm[0], pm[1]), acc2[mm]);   // apart: one rounding of acc a step
+        acc2[mm] = mfma_qk(v, join(pl[0], pl[1]), acc2[mm]);
       }
     }
     ++k;
@@ -783,6 +801,10 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
     if (col < G) {
       const float lse_nat = m * p.scale + logf(l);
       const float inv = 1.f / l;
+      if constexpr (KP == 2) {
+#pragma unroll
+        for (int mm = 0; mm < D / 16; ++mm) acc[mm] += acc2[mm];
+      }
       const int qh = item.kv_head * G + col;
       if (item.out_idx < 0) {
         uint2* orow = reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) +

@@ -45,7 +45,8 @@ def _small_session(wl, mode=0, n_bins=None, split_target=None, free_seed=None, p
                                                 ("f32", 64, 4, 37), ("f32", 128, 4, 37)])
 def test_infinite_values_stay_infinite(dtype, d, gqa, n_bins):
     """An infinity in a retained V row whose weight is above 0 makes that output element infinite, with its sign, and
-    leaves the others alone: probabilities that enter the product in parts have no part that is 0 or negative."""
+    leaves the others alone: probabilities that enter the product in parts have no part that is 0 or negative (weights
+    here are within 2^-60 of the largest)."""
     _gpu()
     g = Geometry(1, 2, 2 * gqa, d, 16, 2)
     wl = custom(61, g, 2, dtype, (50, 400), kv_scale=0.5)
@@ -367,6 +368,71 @@ def test_default_bins_fit_the_vector_kernel(dtype, d, gqa, per_cu):
     assert s.n_bins >= per_cu * torch.cuda.get_device_properties(0).multi_processor_count
     assert s.workers_per_wg() == 1
     compare_layer(s, 0, what=f"{dtype} d{d} gqa{gqa} default bins")
+
+
+@pytest.mark.parametrize("dtype,d,gqa", [("bf16", 64, 1), ("bf16", 64, 3), ("bf16", 64, 16), ("bf16", 128, 4),
+                                         ("f32", 64, 4)])
+def test_infinite_values_at_tiny_weights(dtype, d, gqa):
+    """As above for weights of 2^-100 to 2^-125, near the smallest normal number: scores of whole numbers of bits
+    (sm_scale ln 2) make them exact powers of two, of which a second part of the probability has nothing left."""
+    _gpu()
+    bits = (100, 110, 112, 116, 120, 124, 125)       # all / 64 and / 128 exact in bf16
+    g = Geometry(1, 2, 2 * gqa, d, 16, 2)
+    wl = custom(62, g, 1, dtype, 300, budget=np.ones((1, 2)), jitter=0.0)
+    tables = Tables(wl)
+    td = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    pool = torch.zeros(tables.pool_pages, 2, 2, 16, d, dtype=td)
+    pool[:, 1] = 0.5
+    want = torch.full((1, 2 * gqa, d), 0.5)
+    for i, e in enumerate(bits):
+        row = 5 + 41 * i
+        page = int(tables.pt_pages[int(tables.pt_offsets[0]) + row // 16])
+        pool[page, 0, :, row % 16] = -e / d
+        pool[page, 1, :, row % 16, 3 * i] = np.inf
+        want[..., 3 * i] = np.inf
+    s = DecodeSession(wl, tables=tables, mode=tg.TG_PLAN_AOT_FILL, n_bins=700, pool=pool.cuda(),
+                      q=torch.ones(1, 1, 2 * gqa, d, dtype=td, device="cuda"))
+    s.dplans[0].args.sm_scale = float(np.log(2))
+    s.run_step()
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isinf(s.out[0].float().cpu()), torch.isinf(want))
+    assert torch.allclose(s.out[0].float().cpu(), want, rtol=1e-2)
+
+
+@pytest.mark.parametrize("gqa", [1, 3, 8, 16])
+def test_bf16_d64_probabilities_keep_fp32(gqa):
+    """bf16 head_dim 64: probabilities enter the product with 24 bits.  Pieces of one and two pages leave fp32
+    partials whose error against 64 bits is that of fp32 arithmetic: every weight within 3 units of 2^-24 (score,
+    exponential, product), in outputs that average 16 or 32 of them, so 2e-7 with room for their scatter; with two
+    bf16 parts (2^-17 and a cut on one side) it is 1e-6."""
+    _gpu()
+    g = Geometry(1, 2, 2 * gqa, 64, 16, 2)
+    wl = custom(8500 + gqa, g, 3, "bf16", (900, 1600), kv_scale=0.5)
+    tables = Tables(wl)
+    pool = torch.from_numpy(poisoned_host_pool(wl, tables)).to(torch.bfloat16)
+    pool[:, 1] = pool[:, 1].abs() + 1.0              # terms of one sign: errors are not hidden by what cancels
+    s = DecodeSession(wl, tables=tables, mode=tg.TG_PLAN_AOT_FILL, n_bins=120 if gqa > 4 else 500, fill="host",
+                      pool=pool.cuda())
+    s.run_step()
+    torch.cuda.synchronize()
+    dp, plan, host, q = s.dplans[0], s.plans[0], pool.double().numpy(), s.q[0].double().cpu().numpy()
+    n = plan["num_partials"]
+    part = dp.workspace[: n * gqa * 64 * 4].view(torch.float32).view(n, gqa, 64).double().cpu().numpy()
+    num = den = 0.0
+    for it in plan["items"]:
+        if it["out_idx"] < 0:
+            continue
+        rows = np.arange(int(it["tok_begin"]), int(it["tok_end"]))
+        ids = tables.pt_pages[int(it["pt_base"]) + rows // 16]
+        k, v = (host[ids, j, int(it["slot"]), rows % 16] for j in (0, 1))
+        sc = q[int(it["b"]), int(it["kv_head"]) * gqa: (int(it["kv_head"]) + 1) * gqa] @ k.T / 8.0
+        p = np.exp(sc - sc.max(1, keepdims=True))
+        o = (p @ v) / p.sum(1, keepdims=True)
+        num += ((part[int(it["out_idx"])] - o) ** 2).sum()
+        den += (o ** 2).sum()
+    err = float(np.sqrt(num / den))
+    say(f"bf16 d64 gqa={gqa}: partials {n}, error {err:.3e}")
+    assert n > 100 and err <= 2e-7
 
 
 @pytest.mark.parametrize("d,gqa,chains", [(64, 4, 16), (64, 16, 16), (128, 4, 8), (128, 16, 8)])
