@@ -237,8 +237,9 @@ int32_t tg_build_plan(const tg_geometry* geom, int32_t batch, int32_t layer, con
  * otherwise) runs the items of bin k; an item with out_idx >= 0
  * writes an fp32 partial (o, lse) to the workspace, and the partials of every
  * split unit are combined with a log-sum-exp merge: inside the decode launch
- * when merge_counters is given (bf16, head_dim 128), otherwise by a second
- * launch on the same stream (only when num_partials > 0).
+ * when merge_counters is given (bf16, head_dim 128, fewer than 6 partials per
+ * (b, h) on average), otherwise by a second launch on the same stream (only
+ * when num_partials > 0).
  * All pointers below are DEVICE pointers:
  *   q        [B][Hq][d] dtype
  *   kv_pool  [pool_pages][2][H_p][P][d] dtype (layout in the file header);
@@ -268,9 +269,11 @@ int32_t tg_build_plan(const tg_geometry* geom, int32_t batch, int32_t layer, con
  *            split piece that finishes last merges its unit), so no second
  *            launch is needed.  They must be zero before the first call; every
  *            call leaves them zero, and calls that share them must not overlap
- *            in time.  NULL, or any other dtype / head_dim: the merge runs as a
- *            second launch on the same stream.  The results are the same
- *            either way, bit for bit.
+ *            in time.  NULL, any other dtype / head_dim, or a plan of 6 or more
+ *            partials per (b, h) on average (which one worker would merge one
+ *            after the other): the merge runs as a second launch on the same
+ *            stream and the counters are not touched.  The results are the
+ *            same either way, bit for bit.
  *   append_k, append_v [B][H][d] dtype, or both NULL: this step's new token
  *            of every (b, h), appended inside the launch (needs live_len and a
  *            TG_PLAN_OPEN_END plan, whose one open item per unit does it).

@@ -10,7 +10,8 @@
 // few bins take).  A chunk of a split unit writes an fp32 partial (o, lse), and the partials of every split unit are combined with a
 // log-sum-exp merge (split-KV decoding, Section 2.2.3): by tg_merge_kernel,
 // launched right after on the same stream, or, with arrival counters, inside
-// the head_dim-128 bf16 launch by the piece that finishes last.  The in-launch merge
+// the head_dim-128 bf16 launch by the piece that finishes last (plans of few
+// pieces per unit).  The in-launch merge
 // orders partials and counters with device-scope stores, loads and atomics
 // only: a fence for ordinary stores would write back and invalidate the whole
 // L2 of an XCD.
@@ -137,7 +138,6 @@ struct DecodeParams {
   float scale_log2;          // sm_scale * log2(e)
   float scale;               // sm_scale
   int32_t* merge_counters;   // [B*H] arrival counters of the in-launch merge, or NULL
-  int32_t merge_lanes;       // chains a unit's partials are merged in (merge_lanes() below)
   // in-launch decode-token append (open items only), or append_k == NULL
   const u4* append_k;        // [B][H] token rows, 16-byte chunks
   const u4* append_v;
@@ -881,67 +881,47 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
         const int s = unit_splits[u], base = unit_base[u];
         if (__builtin_amdgcn_readfirstlane(arrived[j]) != s - 1) continue;
         if (col < G) {
-          // the same chains (piece i in chain i mod merge_lanes), the same
-          // recurrence and the same order as the merge kernels
-          const int lanes = p.merge_lanes;
-          float M = -INFINITY;   // the largest lse, which the chains are combined at
-          if (lanes > 1)
-            for (int i = 0; i < s; ++i)
-              M = fmaxf(M, __hip_atomic_load(p.part_lse + ((int64_t)base + i) * G + col, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT));
-          float L = 0.f;
+          float mr = -INFINITY, L = 0.f;
           f32x4 A[8];
 #pragma unroll
           for (int mm = 0; mm < 8; ++mm) A[mm] = f32x4{0.f, 0.f, 0.f, 0.f};
-          for (int w = 0; w < min(lanes, s); ++w) {
-            float mr = -INFINITY, Lc = 0.f;
-            f32x4 Ac[8];
+          // up to kSplitBatch partials are requested before the first is
+          // used: one round trip for a unit of that many splits (indices past
+          // the last re-read it, and selects discard their steps)
+          constexpr int kSplitBatch = 4;
+          for (int i0 = 0; i0 < s; i0 += kSplitBatch) {
+            float lv[kSplitBatch];
+            f32x4 ov[kSplitBatch][8];
 #pragma unroll
-            for (int mm = 0; mm < 8; ++mm) Ac[mm] = f32x4{0.f, 0.f, 0.f, 0.f};
-            // up to kSplitBatch partials are requested before the first is
-            // used: one round trip for a chain of that many splits (indices
-            // past the last re-read it, and selects discard their steps)
-            constexpr int kSplitBatch = 4;
-            for (int i0 = w; i0 < s; i0 += kSplitBatch * lanes) {
-              float lv[kSplitBatch];
-              f32x4 ov[kSplitBatch][8];
+            for (int jj = 0; jj < kSplitBatch; ++jj) {
+              const int64_t pidx = (int64_t)base + min(i0 + jj, s - 1);
+              lv[jj] = __hip_atomic_load(p.part_lse + pidx * G + col, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              const uint64_t* prow = reinterpret_cast<const uint64_t*>(p.part_o + (pidx * G + col) * D + 4 * rb);
 #pragma unroll
-              for (int jj = 0; jj < kSplitBatch; ++jj) {
-                const int64_t pidx = (int64_t)base + min(i0 + jj * lanes, s - 1);
-                lv[jj] = __hip_atomic_load(p.part_lse + pidx * G + col, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const uint64_t* prow = reinterpret_cast<const uint64_t*>(p.part_o + (pidx * G + col) * D + 4 * rb);
-#pragma unroll
-                for (int mm = 0; mm < 8; ++mm) {
-                  const uint64_t lo = __hip_atomic_load(prow + mm * 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                  const uint64_t hi = __hip_atomic_load(prow + mm * 8 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                  ov[jj][mm] = f32x4{__uint_as_float((uint32_t)lo), __uint_as_float((uint32_t)(lo >> 32)),
-                                     __uint_as_float((uint32_t)hi), __uint_as_float((uint32_t)(hi >> 32))};
-                }
-              }
-#pragma unroll
-              for (int jj = 0; jj < kSplitBatch; ++jj) {
-                const bool use = i0 + jj * lanes < s;
-                const float mn = fmaxf(mr, lv[jj]);
-                const float a = __expf(mr - mn), wt = __expf(lv[jj] - mn);
-                const float Ln = fmaf(Lc, a, wt);
-#pragma unroll
-                for (int mm = 0; mm < 8; ++mm)
-#pragma unroll
-                  for (int q = 0; q < 4; ++q) {
-                    const float An = fmaf(Ac[mm][q], a, wt * ov[jj][mm][q]);
-                    Ac[mm][q] = use ? An : Ac[mm][q];
-                  }
-                Lc = use ? Ln : Lc;
-                mr = use ? mn : mr;
+              for (int mm = 0; mm < 8; ++mm) {
+                const uint64_t lo = __hip_atomic_load(prow + mm * 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint64_t hi = __hip_atomic_load(prow + mm * 8 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                ov[jj][mm] = f32x4{__uint_as_float((uint32_t)lo), __uint_as_float((uint32_t)(lo >> 32)),
+                                   __uint_as_float((uint32_t)hi), __uint_as_float((uint32_t)(hi >> 32))};
               }
             }
-            if (lanes == 1) M = mr;
-            const float f = lanes == 1 ? 1.f : __expf(mr - M);
-            L = fmaf(Lc, f, L);
+            // the same running-max recurrence, in the same order, as tg_merge_kernel
 #pragma unroll
-            for (int mm = 0; mm < 8; ++mm)
+            for (int jj = 0; jj < kSplitBatch; ++jj) {
+              const bool use = i0 + jj < s;
+              const float mn = fmaxf(mr, lv[jj]);
+              const float a = __expf(mr - mn), w = __expf(lv[jj] - mn);
+              const float Ln = fmaf(L, a, w);
 #pragma unroll
-              for (int q = 0; q < 4; ++q) A[mm][q] = fmaf(Ac[mm][q], f, A[mm][q]);
+              for (int mm = 0; mm < 8; ++mm)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                  const float An = fmaf(A[mm][q], a, w * ov[jj][mm][q]);
+                  A[mm][q] = use ? An : A[mm][q];
+                }
+              L = use ? Ln : L;
+              mr = use ? mn : mr;
+            }
           }
           const int qh = h * G + col;
           uint2* orow =
@@ -951,7 +931,7 @@ __global__ void __launch_bounds__(kBlock) tg_decode_mfma_kernel(DecodeParams p, 
             orow[mm * 4] =
                 make_uint2(uint32_t(f32_to_bf16(A[mm][0] / L)) | (uint32_t(f32_to_bf16(A[mm][1] / L)) << 16),
                            uint32_t(f32_to_bf16(A[mm][2] / L)) | (uint32_t(f32_to_bf16(A[mm][3] / L)) << 16));
-          if (p.lse && rb == 0) p.lse[(int64_t)b * p.num_q_heads + qh] = M + logf(L);
+          if (p.lse && rb == 0) p.lse[(int64_t)b * p.num_q_heads + qh] = mr + logf(L);
         }
         if (lane == 0) __hip_atomic_store(p.merge_counters + u, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
@@ -1586,10 +1566,15 @@ int32_t decode_impl(const tg_decode_args* a, void* ws_ptr, size_t ws_bytes, void
   p.live_w = a->append_k ? a->live_len + (int64_t)a->layer * g.num_kv_heads : nullptr;
   p.append_full = a->append_full;
   // the bf16 head_dim-128 kernel merges split units inside its launch when the
-  // caller passes arrival counters; every other case merges in a second launch
-  const bool fused_merge = a->merge_counters && a->num_partials > 0 && a->dtype == TG_BF16 && g.head_dim == 128;
+  // caller passes arrival counters and one chain is enough; every other case
+  // merges in a second launch.  With several chains one wave would walk them
+  // all: 24 requests of 2000 to 16000 tokens (6.2 pieces per unit) 92 us there,
+  // 65 in one chain there, 53 with the second launch; 16 requests (8.9) 76, 52
+  // and 36; one of 40000 tokens (129) 211, 158 and 17.
+  const int lanes = merge_lanes(a->num_partials, (int64_t)a->batch * g.num_kv_heads);
+  const bool fused_merge =
+      a->merge_counters && a->num_partials > 0 && lanes == 1 && a->dtype == TG_BF16 && g.head_dim == 128;
   p.merge_counters = fused_merge ? a->merge_counters : nullptr;
-  p.merge_lanes = merge_lanes(a->num_partials, (int64_t)a->batch * g.num_kv_heads);
   p.scale = a->sm_scale != 0.f ? a->sm_scale : 1.0f / std::sqrt((float)g.head_dim);
   p.scale_log2 = p.scale * kLog2e;
   if (a->num_items == 0) return TG_OK;
@@ -1603,10 +1588,10 @@ int32_t decode_impl(const tg_decode_args* a, void* ws_ptr, size_t ws_bytes, void
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "decode launch failed: %s", hipGetErrorString(e));
   if (a->num_partials > 0 && !fused_merge) {
-    MergeFn mf = pick_merge(a->dtype, g.head_dim, p.merge_lanes);
+    MergeFn mf = pick_merge(a->dtype, g.head_dim, lanes);
     // one chain: four outputs per thread; several: a workgroup per (unit, head), D/4 threads per chain
-    const int block = p.merge_lanes == 1 ? kBlock : g.head_dim / 4 * p.merge_lanes;
-    const int grid_y = p.merge_lanes == 1 ? (gqa * g.head_dim / 4 + kBlock - 1) / kBlock : gqa;
+    const int block = lanes == 1 ? kBlock : g.head_dim / 4 * lanes;
+    const int grid_y = lanes == 1 ? (gqa * g.head_dim / 4 + kBlock - 1) / kBlock : gqa;
     hipLaunchKernelGGL(mf, dim3(a->batch * g.num_kv_heads, grid_y), dim3(block), 0, st, a->unit_splits,
                        a->unit_partial_base, p.part_o, p.part_lse, a->out, a->lse, g.num_kv_heads, gqa);
     e = hipGetLastError();
