@@ -138,7 +138,7 @@ struct PrefillParams {
 // Measured, whole blocks against cut ones: one request, head_dim 128, chunk
 // 512 over a 16384-token history 440 -> 76 us, chunk 16 over 8192 153 -> 20
 // us; four requests, chunk 512 over 8192 166 -> 117 us; head_dim 64, five
-// requests, chunk 333, 74 -> 50 us.  Where no block is much longer than the
+// requests, chunk 333, 74 -> 45 us.  Where no block is much longer than the
 // mean per CU the merge costs more than the cut saves (four requests, chunk
 // 512 over 2048 tokens: 61 against 72 us): the caller gives no workspace there.
 constexpr int kSplitMinTiles = 3;
@@ -162,9 +162,11 @@ __device__ __forceinline__ uint32_t lds_address(const void* ptr) {
   return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const TG_LDS void*)ptr));
 }
 
-// 16 bytes per lane from global memory into LDS at m0_base + 16 * lane.
-__device__ __forceinline__ void lds_dma16(const void* src, uint32_t m0_base) {
-  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(m0_base) : "memory");
+// 16 bytes per lane from global memory (a wave-uniform base plus 16 * chunk
+// bytes per lane) into LDS at m0_base + 16 * lane.  The scalar base keeps
+// 64-bit addresses out of the vector registers.
+__device__ __forceinline__ void lds_dma16(const u4* base, uint32_t chunk, uint32_t m0_base) {
+  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(chunk * 16), "s"(base), "{m0}"(m0_base) : "memory");
 }
 
 template <int N>
@@ -196,6 +198,11 @@ __device__ __forceinline__ int wave_inclusive_sum(int x) {
   return x;
 }
 
+// Registers: 222 and 226 (key-split) at head_dim 128, 128 at 64, none in scratch.
+// A reload from scratch would wait for every DMA in flight: with 64-bit lane
+// addresses for the DMA, six reloads a tile at head_dim 64 drained the ring
+// (five requests, chunk 333, 49.4 us against 45.1; the blocks of one request,
+// chunk 512 over 16384 tokens, 58 against 54).
 template <int D, bool kSplit, int kWavesPerSimd>
 __global__ void __launch_bounds__(kBlock, kWavesPerSimd) tg_prefill_kernel(PrefillParams p) {
   using S = Shape<D>;
@@ -337,21 +344,21 @@ __global__ void __launch_bounds__(kBlock, kWavesPerSimd) tg_prefill_kernel(Prefi
 #pragma unroll
       for (int j = 0; j < kDmaInst; ++j) {
         const int r = rb0 + j * kRowsPerDma + rl;   // key row within the page (== tile row mod 16)
-        lds_dma16(kb + r * kChunks + (pos ^ S::k_swz(r)), dst + j * 1024);
-        lds_dma16(vb + r * kChunks + (pos ^ S::v_swz(r)), dst + kTile * kChunks * 16 + j * 1024);
+        lds_dma16(kb, r * kChunks + (pos ^ S::k_swz(r)), dst + j * 1024);
+        lds_dma16(vb, r * kChunks + (pos ^ S::v_swz(r)), dst + kTile * kChunks * 16 + j * 1024);
       }
     } else {
-      const int c0 = (t - n_hist_tiles) * kTile + wave * kDmaRows;   // first chunk key of the share
-      const u4* kb = p.k_new + h * kChunks;
-      const u4* vb = p.v_new + h * kChunks;
+      const int c0 = min((t - n_hist_tiles) * kTile + wave * kDmaRows, C - 1);   // first chunk key of the share
+      const int64_t first = (((int64_t)b * C + c0) * p.num_kv_heads + h) * kChunks;
+      const u4* kb = p.k_new + first;
+      const u4* vb = p.v_new + first;
 #pragma unroll
       for (int j = 0; j < kDmaInst; ++j) {
         const int r = j * kRowsPerDma + rl;
-        const int c = min(c0 + r, C - 1);   // rows past the chunk repeat its last key (masked later)
         const int rr = rb0 + r;             // tile row mod 16
-        const int64_t roff = ((int64_t)b * C + c) * p.num_kv_heads * kChunks;
-        lds_dma16(kb + roff + (pos ^ S::k_swz(rr)), dst + j * 1024);
-        lds_dma16(vb + roff + (pos ^ S::v_swz(rr)), dst + kTile * kChunks * 16 + j * 1024);
+        const int roff = min(r, C - 1 - c0) * p.num_kv_heads * kChunks;   // rows past the chunk repeat its last key (masked later)
+        lds_dma16(kb, roff + (pos ^ S::k_swz(rr)), dst + j * 1024);
+        lds_dma16(vb, roff + (pos ^ S::v_swz(rr)), dst + kTile * kChunks * 16 + j * 1024);
       }
     }
   };
@@ -719,11 +726,15 @@ int32_t tg_prefill(const tg_prefill_args* a, void* hip_stream) {
     if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "prefill merge launch failed: %s", hipGetErrorString(e));
     return TG_OK;
   }
-  // head_dim 64: two workgroups fit a CU (64 KiB rings) at 128 registers, which
-  // pays once there are more than two blocks per CU
-  auto kernel = g.head_dim == 128 ? tg_prefill_kernel<128, false, 2>
-                                  : (blocks > 512 ? tg_prefill_kernel<64, false, 4> : tg_prefill_kernel<64, false, 2>);
-  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, st, p);
+  // head_dim 64: two workgroups fit a CU (64 KiB rings, 128 registers), which
+  // pays once there are more than two blocks per CU: 1024 blocks (16 requests,
+  // chunk 512 over 4096) 177 -> 150 us, 640 blocks 91 -> 90.  Fewer blocks even
+  // out better over the CUs one at a time, the longest first (512 blocks of 8
+  // requests 63 us against 65, 336 of 14 37 against 38): LDS that is not used
+  // keeps the second workgroup off.
+  const size_t one_per_cu = g.head_dim == 64 && blocks <= 512 ? 24 << 10 : 0;
+  auto kernel = g.head_dim == 128 ? tg_prefill_kernel<128, false, 2> : tg_prefill_kernel<64, false, 2>;
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), one_per_cu, st, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return tg::fail(TG_ERR_HIP, "prefill launch failed: %s", hipGetErrorString(e));
   return TG_OK;
