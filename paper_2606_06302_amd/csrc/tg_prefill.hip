@@ -229,7 +229,7 @@ __global__ void __launch_bounds__(kBlock, kWavesPerSimd) tg_prefill_kernel(Prefi
 
   // block -> (unit, row tile): the host schedule, or units round-robin over
   // the 8 XCDs (all row tiles of a unit on one XCD either way); in the
-  // key-split launch, the blocks of this worker's run
+  // key-split launch, this workgroup's piece of a block
   int unit, rt;
   int piece = 0, first_slot = 0, piece_tiles = 0;   // key-split launch
   if constexpr (kSplit) {
@@ -496,14 +496,16 @@ __global__ void __launch_bounds__(kBlock, kWavesPerSimd) tg_prefill_kernel(Prefi
         const bool raise = (mx - m[cb]) * cs > kSlack;
         if (__any(raise)) {   // raise the running max (rare after the first block)
           const float m_new = raise ? mx : m[cb];
-          const float alpha = fast_exp2((m[cb] - m_new) * cs);   // 0 when m was -inf
+          // 0 when m was -inf, and 1, not NaN, where it still is beside a row that raises
+          const float alpha = kSplit && !raise ? 1.f : fast_exp2((m[cb] - m_new) * cs);
           m[cb] = m_new;
           l[cb] *= alpha;
 #pragma unroll
           for (int d = 0; d < S::kDB; ++d) acc[cb][d] *= alpha;
         }
-        // a piece may start with chunk keys that lie in the future of a row: its
-        // maximum is still -inf then, and its probabilities must be 0, not NaN
+        // key-split launch: a row whose scores so far are all -inf has no
+        // probabilities yet, not NaN (rows past the chunk's end are such, and
+        // rows that meet infinite scores first)
         const float mcs = (kSplit && m[cb] == -INFINITY ? 0.f : m[cb]) * cs;
         uint32_t pw[8];
 #pragma unroll
@@ -602,7 +604,8 @@ __global__ void __launch_bounds__(256) tg_prefill_merge_kernel(PrefillParams p) 
     float Mn = M;
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) Mn = fmaxf(Mn, mv[j]);
-    // no visible key so far: nothing to rescale, and the weights below are 0
+    // a piece of chunk tiles that all lie in a wave's future leaves m = -inf and
+    // zeros; while there is no other, nothing is rescaled and the weights are 0
     const float Mr = Mn == -INFINITY ? 0.f : Mn;
     const float a = fast_exp2((M - Mr) * p.scale_log2);
     L *= a;

@@ -202,6 +202,37 @@ def test_prefill_key_split_clamps_lengths(d):
     _compare(ps, [(b, q) for b in range(wl.batch) for q in range(g.num_q_heads)], "clamped lengths, key split")
 
 
+@pytest.mark.parametrize("d", [128, 64])
+def test_prefill_key_split_rows_with_infinite_scores_first(d):
+    """Rows whose scores overflow to -inf over the first keys, beside rows of the same wave whose scores there are
+    finite and raise the running maximum: the key-split launch gives the keys of score -inf no weight."""
+    _gpu()
+    g = Geometry(1, 1, 4, d, 16, 1)
+    wl = custom(655, g, 1, "bf16", 2000, chunk_len=24, budget=np.ones((1, 1)), jitter=0.0)
+    tables = Tables(wl)
+    pool = torch.from_numpy(poisoned_host_pool(wl, tables)).to(torch.bfloat16)
+    n = int(tables.kv_len[0, 0, 0])
+    ids = torch.from_numpy(tables.pt_pages[: (n + 15) // 16].astype(np.int64))
+    pool[:, 0, ..., 0] = 0.0
+    pool[ids[:5], 0, 0, :, 0] = -3e38                    # the first 80 keys
+    ps = PrefillSession(wl, tables=tables, fill="host", pool=pool.cuda())
+    ps.k_new[..., 0] = 0.0
+    ps.q[..., 0] = 0.0
+    ps.q[:, :, 1::2, 0] = 3.0                            # every other row: 3 x -3e38 is -inf in fp32
+    assert _give_workspace(ps)
+    ps.run()
+    torch.cuda.synchronize()
+    out, q = ps.out[0].double().cpu().numpy(), ps.q[0].double().cpu().numpy()
+    k, v = (np.concatenate([pool[ids, j, 0].double().numpy().reshape(-1, d)[:n], x[0, :, 0].double().cpu().numpy()])
+            for j, x in ((0, ps.k_new), (1, ps.v_new)))
+    for i in range(24):
+        for j in range(4):
+            sc = (k[: n + i + 1] @ q[i, j]) / np.sqrt(d)
+            sc[:80] = -np.inf if j % 2 else sc[:80]
+            p = np.exp(sc - sc.max())
+            check_close(out[i, j][None], (p @ v[: n + i + 1])[None] / p.sum(), "bf16", f"row {i} head {j}")
+
+
 @pytest.mark.parametrize("plan", ["fill", "aot"])
 def test_prefill_chunk_of_one_matches_decode_path(plan):
     """C = 1: one chunk row of chunked prefill (Section 2.2.1) sees exactly what the split-KV decode path
