@@ -160,6 +160,12 @@ int32_t tg_split_map(const tg_geometry* geom, const double* budget, const int32_
  * TG_ERR_HIP if the device query fails. */
 int32_t tg_decode_max_ctas(const tg_geometry* geom, int32_t dtype, int32_t device, int32_t* n_cta);
 
+/* Consecutive bins that one workgroup of the decode launch runs, for a plan of
+ * n_bins >= 1 bins (host only): bin k runs in workgroup k / bins, workgroups go
+ * to the XCDs round-robin.  bins out.  Errors: TG_ERR_INVALID_ARG,
+ * TG_ERR_UNSUPPORTED as tg_decode_max_ctas. */
+int32_t tg_decode_bins_per_workgroup(const tg_geometry* geom, int32_t dtype, int32_t n_bins, int32_t* bins);
+
 /* ------------------------------- 2b. balanced split-KV partition of a layer
  * Algorithm 1's rule "workgroups proportional to budget share, at least one"
  * applied to this batch's integer retained lengths, with work unit

@@ -7,14 +7,14 @@
 // cuts every (b, h) into page-aligned chunks and places them on n_bins bins;
 // worker k of the launch runs bin k (a wave in the bf16 matrix-core kernel, a
 // workgroup in the fp32 one and in the vector kernel, which few query heads and
-// few bins take).  A chunk of a split unit writes an fp32 partial (o, lse), and the partials of every split unit are combined with a
-// log-sum-exp merge (split-KV decoding, Section 2.2.3): by tg_merge_kernel,
-// launched right after on the same stream, or, with arrival counters, inside
-// the head_dim-128 bf16 launch by the piece that finishes last (plans of few
-// pieces per unit).  The in-launch merge
-// orders partials and counters with device-scope stores, loads and atomics
-// only: a fence for ordinary stores would write back and invalidate the whole
-// L2 of an XCD.
+// few bins take).  A chunk of a split unit writes an fp32 partial (o, lse), and
+// the partials of every split unit are combined with a log-sum-exp merge
+// (split-KV decoding, Section 2.2.3): by a merge kernel launched right after on
+// the same stream, or, with arrival counters, inside the head_dim-128 bf16
+// launch by the piece that finishes last (plans of few pieces per unit).  The
+// in-launch merge orders partials and counters with device-scope stores, loads
+// and atomics only: a fence for ordinary stores would write back and invalidate
+// the whole L2 of an XCD.
 //
 // Open-ended items (the chunk that ends a unit in a plan built for several
 // steps) run to the unit's live length, and can append the step's new token
@@ -1457,13 +1457,20 @@ bool wave_per_bin(int dtype, int d, int gqa, int n_bins) {
 
 // Waves per workgroup of the bf16 kernel, each with a bin of its own.  Its LDS
 // limits a CU to one workgroup of up to four waves, so plans of fewer bins than
-// four per CU take fewer waves per workgroup and use every CU: 256 bins, gqa 4,
-// 16 requests of 8192 tokens 60.5 -> 58.2 us at head_dim 128, 38.8 -> 36.6 at
-// 64.
+// four per CU take fewer waves per workgroup and spread over more CUs: over all
+// of them at multiples of 256 bins, over 129 to 255 between, where the time
+// keeps falling with the bins (16 requests of 8192 tokens, gqa 4, 256 / 257 /
+// 300 / 400 / 512 / 513 / 768 / 1024 bins: 62 / 63 / 54 / 43 / 36 / 36 / 29 / 29
+// us at head_dim 128, 32 / 33 / 32 / 31 / 26 / 27 / 21 / 19 at 64).  256 bins in
+// workgroups of four: 60.5 against 58.2 us at 128, 38.8 against 36.6 at 64.
 int waves_per_wg(int n_bins) {
   constexpr int kCus = 256;
   const int w = n_bins / kCus + (n_bins % kCus != 0);
   return w < kWaves ? w : kWaves;
+}
+
+int bins_per_wg(int dtype, int d, int gqa, int n_bins) {
+  return wave_per_bin(dtype, d, gqa, n_bins) ? waves_per_wg(n_bins) : 1;
 }
 
 int32_t check_decode_shape(const tg_geometry* g, int dtype) {
@@ -1580,9 +1587,8 @@ int32_t decode_impl(const tg_decode_args* a, void* ws_ptr, size_t ws_bytes, void
   if (a->num_items == 0) return TG_OK;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   DecodeFn fn = pick_decode(a->dtype, g.head_dim, gqa, a->n_bins);
-  const bool wave_bins = wave_per_bin(a->dtype, g.head_dim, gqa, a->n_bins);
-  const int waves = wave_bins ? waves_per_wg(a->n_bins) : kWaves;
-  const int bins = wave_bins ? waves : 1;   // bins per workgroup
+  const int bins = bins_per_wg(a->dtype, g.head_dim, gqa, a->n_bins);   // bins per workgroup
+  const int waves = wave_per_bin(a->dtype, g.head_dim, gqa, a->n_bins) ? bins : kWaves;
   hipLaunchKernelGGL(fn, dim3((a->n_bins + bins - 1) / bins), dim3(64 * waves), 0, st, p, a->items, a->pt_pages,
                      a->bin_offsets, p.pool);
   hipError_t e = hipGetLastError();
@@ -1613,6 +1619,14 @@ size_t tg_decode_workspace_bytes(const tg_geometry* geom, int32_t batch, int32_t
   // fp32 partial outputs, then their lse
   return align256((size_t)num_partials * gqa * d * sizeof(float)) +
          align256((size_t)num_partials * gqa * sizeof(float));
+}
+
+int32_t tg_decode_bins_per_workgroup(const tg_geometry* geom, int32_t dtype, int32_t n_bins, int32_t* bins) {
+  if (!bins) return tg::fail(TG_ERR_INVALID_ARG, "bins is NULL");
+  if (n_bins < 1) return tg::fail(TG_ERR_INVALID_ARG, "n_bins must be >= 1");
+  if (int32_t rc = check_decode_shape(geom, dtype)) return rc;
+  *bins = bins_per_wg(dtype, geom->head_dim, geom->num_q_heads / geom->num_kv_heads, n_bins);
+  return TG_OK;
 }
 
 int32_t tg_decode_max_ctas(const tg_geometry* geom, int32_t dtype, int32_t device, int32_t* n_cta) {

@@ -141,13 +141,8 @@ class DecodeSession:
         return end - items["tok_begin"]
 
     def workers_per_wg(self):
-        """Bins (workers) per workgroup of the decode kernel the library picks for this session: in the
-        bf16 kernel up to four waves, each its own worker (fewer for plans of under four bins per CU);
-        one otherwise (fp32, and head_dim 64 with one query head, or with few bins and up to four)."""
-        g = self.wl.geom
-        if self.tg_dtype != tg.TG_BF16 or (g.head_dim == 64 and (g.gqa == 1 or (g.gqa <= 4 and self.n_bins <= 384))):
-            return 1
-        return min(4, -(-self.n_bins // 256))
+        """Bins (workers) per workgroup of the decode kernel the library picks for this session."""
+        return tg.tg_decode_bins_per_workgroup(self.wl.geom, self.tg_dtype, self.n_bins)
 
     def calibrate_xcd_weights(self, stream=None, classes=8, per_layer=False):
         """Measures every worker's pages per microsecond over one stamped step and rebuilds the

@@ -113,6 +113,7 @@ _SIGS = {
     "tg_reserve": (_i32, [_G, _i32, _P, _P, _P, _P, _P, _P, _i64, _i64, _P, _P, _P, _P, _i64, _P]),
     "tg_split_map": (_i32, [_G, _P, _P, _i32, _P]),
     "tg_decode_max_ctas": (_i32, [_G, _i32, _i32, _P]),
+    "tg_decode_bins_per_workgroup": (_i32, [_G, _i32, _i32, _P]),
     "tg_build_plan": (_i32, [_G, _i32, _i32, _P, _P, _P, _P, _i32, _i32, _i32, _P, _P, _i32, _P, _i32, _P, _P,
                              _P, _P, _P]),
     "tg_decode_workspace_bytes": (_sz, [_G, _i32, _i32]),
@@ -226,6 +227,14 @@ def tg_decode_max_ctas(geom, dtype, device=0) -> int:
     g = _geom(geom)
     n = C.c_int32(0)
     _check(_lib.tg_decode_max_ctas(C.byref(g), int(dtype), int(device), C.byref(n)), "tg_decode_max_ctas")
+    return n.value
+
+
+def tg_decode_bins_per_workgroup(geom, dtype, n_bins) -> int:
+    g = _geom(geom)
+    n = C.c_int32(0)
+    _check(_lib.tg_decode_bins_per_workgroup(C.byref(g), int(dtype), int(n_bins), C.byref(n)),
+           "tg_decode_bins_per_workgroup")
     return n.value
 
 

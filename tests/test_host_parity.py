@@ -663,3 +663,21 @@ def test_release_and_concat_bit_exact(cfg):
         e2, q2 = oracle.concat_tables(off, pages, again["pt_offsets"], again["pt_pages"])
         assert np.array_equal(o2, e2) and np.array_equal(p2, q2)
         assert sorted(p2.tolist()) == sorted(res["pt_pages"].tolist())
+
+
+@pytest.mark.parametrize("dtype,d,gqa,n_bins,want", [
+    (tg.TG_BF16, 128, 8, 1, 1), (tg.TG_BF16, 128, 8, 256, 1), (tg.TG_BF16, 128, 8, 257, 2), (tg.TG_BF16, 128, 1, 512, 2),
+    (tg.TG_BF16, 128, 16, 768, 3), (tg.TG_BF16, 128, 8, 769, 4), (tg.TG_BF16, 128, 8, 2 ** 31 - 1, 4),
+    (tg.TG_BF16, 64, 1, 1792, 1), (tg.TG_BF16, 64, 4, 384, 1), (tg.TG_BF16, 64, 4, 385, 2), (tg.TG_BF16, 64, 5, 200, 1),
+    (tg.TG_BF16, 64, 5, 1024, 4), (tg.TG_F32, 64, 2, 1024, 1), (tg.TG_F32, 128, 16, 1024, 1)])
+def test_bins_per_decode_workgroup(dtype, d, gqa, n_bins, want):
+    """One to four bins per workgroup where every wave runs its own (bf16 matrix kernel, by plan size), else one: the
+    mapping from bins to workgroups, and so to XCDs, that weights and time stamps are grouped by."""
+    assert tg.tg_decode_bins_per_workgroup(Geometry(1, 2, 2 * gqa, d, 16, 2), dtype, n_bins) == want
+
+
+def test_bins_per_decode_workgroup_refuses():
+    for geom, dtype, n_bins in ((Geometry(1, 2, 2, 128, 16, 2), tg.TG_BF16, 0), (Geometry(1, 2, 2, 96, 16, 2), tg.TG_BF16, 8),
+                                (Geometry(1, 2, 34, 128, 16, 2), tg.TG_BF16, 8), (Geometry(1, 2, 2, 128, 16, 2), 7, 8)):
+        with pytest.raises(tg.TangramError):
+            tg.tg_decode_bins_per_workgroup(geom, dtype, n_bins)
