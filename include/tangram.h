@@ -409,9 +409,13 @@ int32_t tg_append(const tg_append_args* args, void* hip_stream);
  *   the key-split launch: blocks much longer than the others are cut by keys,
  *   their fp32 partials merged by a second launch on the same stream, and
  *   block_order is not used.  It pays where the longest block, in tiles, is
- *   longer than about 1.25 times the launch's tiles / 208, plus 12: few
- *   requests, or very unequal histories.  The size is 0, and a workspace is
- *   not used, past 512 (request, KV head) units or 1024 blocks; one that is
+ *   longer than about 1.25 times the launch's tiles / 208, plus 12 (head_dim
+ *   128), or 2 times the tiles / 448, plus 10 (64): few
+ *   requests, or very unequal histories.  The caller decides by giving a
+ *   workspace or none.  The size does not grow with the batch or the history,
+ *   55 MB at head_dim 128 and 60 MB at 64 once chunk_len * gqa reaches 256;
+ *   layers that run one after another can share one.  It is 0, and a workspace
+ *   is not used, past 512 (request, KV head) units or 1024 blocks; one that is
  *   too small or not 16-byte aligned is not used either.
  * Supported: dtype TG_BF16, head_dim 64 or 128, page_size 16, gqa 1..16,
  * chunk_len >= 1. */

@@ -147,8 +147,9 @@ constexpr int kSplitMaxBlocks = 1024;    // past it blocks outnumber the CUs by 
 // Pieces to aim at: a little under the workgroups that run at once (one per CU
 // at head_dim 128, two at 64), because cutting into equal pieces rounds up.
 // One request, chunk 512, 16384 tokens, with 160 / 208 / 256 / 320: 94 / 81 /
-// 110 / 99 us at 128; two requests with 208 / 352 / 448 / 512: 84 / 78 / 70 /
-// 86 us at 64.
+// 110 / 99 us at 128.  At 64, chunk 512, with 352 / 448 / 512: one request over
+// 16384 tokens 60 / 56 / 65 us, two over 8192 61 / 57 / 68, four 95 / 109 / 110;
+// over 57 shapes 0.99 / 1 / 1.02.
 constexpr int split_target(int d) { return d == 128 ? 208 : 448; }
 // a cut unit of n tiles has at most n / T + 1 <= 2n / T pieces
 constexpr int split_slots(int d) { return 2 * split_target(d); }

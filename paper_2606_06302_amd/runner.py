@@ -317,6 +317,22 @@ class DecodeSession:
 REALTIME_HZ = 100e6
 
 
+def split_pays(head_dim, chunk_len, gqa, hist) -> bool:
+    """Whether cutting the longest prefill blocks by keys beats launching whole blocks, for one layer's retained
+    history lengths hist ([B][H], or flat): the longest block's key tiles bound the whole-block launch, the even
+    share of the pieces it aims at (208 at head_dim 128, 448 at 64) the key-split one, which adds a merge that grows
+    with the rows of a block.  Whole blocks of head_dim 64 share a CU in pairs and even out better, so their share
+    weighs more.  The lines are fitted to 523 shapes measured both ways, 1 to 48 requests, chunks of 16 to 4096 over
+    200 to 16384 tokens.  Where they choose the slower launch: at 128, cut 4 of 259 shapes at a loss of 3 to 10 %; at
+    64, 4 of 264 at 4 to 12 %; the others lose a gain (at 128 up to 1.74 times, in a launch of a few very long
+    blocks; at 64 up to 1.09)."""
+    rows, last = chunk_len * gqa, (chunk_len - 1) // 64 + 1          # 256 query rows per block, 64 keys per tile
+    tiles = -(-np.asarray(hist, dtype=np.int64) // 64) + last        # of every unit's last row tile
+    total, block = float(tiles.sum()) * -(-rows // 256), min(rows, 256) / 256
+    line = 1.25 * total / 208 + 3 + 9 * block if head_dim == 128 else 2 * total / 448 + 5 + 5 * block
+    return float(tiles.max()) >= line
+
+
 class PrefillSession:
     """Pool, chunk inputs and output of one chunked-prefill workload (one layer)."""
 
@@ -362,21 +378,11 @@ class PrefillSession:
                                          self.pool, self.t.d_pt_pages, self.d_offsets, self.d_kv_len,
                                          self.d_group_of, self.d_slot_of, self.out, block_order=self.d_order)
         # scheduled ahead of time: partials of the key-split launch where it pays
-        ws_bytes = tg.tg_prefill_workspace_bytes(self.args) if schedule and self._split_pays() else 0
+        pays = schedule and split_pays(g.head_dim, C, g.gqa, self.hist[:, layer])
+        ws_bytes = tg.tg_prefill_workspace_bytes(self.args) if pays else 0
         if ws_bytes:
             self.workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=device)
             self.args.workspace, self.args.workspace_bytes = self.workspace.data_ptr(), ws_bytes
-
-    def _split_pays(self) -> bool:
-        """Whether cutting the longest blocks by keys beats launching whole blocks: the longest block's key tiles
-        bound the whole-block launch, the even share of 208 pieces the key-split one, which adds a merge that grows
-        with the rows of a block.  The line is fitted to 50 shapes measured both ways: with 1 to 60 requests, chunks
-        of 16 to 512 over 400 to 16384 tokens it misses at most 10 % of either side."""
-        g, C = self.wl.geom, self.wl.chunk_len
-        rows, last = C * g.gqa, (C - 1) // 64 + 1          # 256 query rows per block, 64 keys per tile
-        tiles = -(-self.hist[:, self.layer].astype(np.int64) // 64) + last      # of every unit's last row tile
-        share = float(tiles.sum()) * -(-rows // 256) / 208
-        return float(tiles.max()) >= 1.25 * share + 3 + 9 * min(rows, 256) / 256
 
     def run(self, stream=None):
         tg.tg_prefill(self.args, stream)

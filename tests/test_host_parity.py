@@ -681,3 +681,19 @@ def test_bins_per_decode_workgroup_refuses():
                                 (Geometry(1, 2, 34, 128, 16, 2), tg.TG_BF16, 8), (Geometry(1, 2, 2, 128, 16, 2), 7, 8)):
         with pytest.raises(tg.TangramError):
             tg.tg_decode_bins_per_workgroup(geom, dtype, n_bins)
+
+
+@pytest.mark.parametrize("d,B,H,gqa,C,hist,pays", [
+    (128, 1, 8, 4, 512, 13000, True),       # one request, a long history
+    (128, 16, 8, 4, 512, 4000, False),      # blocks enough, of one length
+    (64, 1, 8, 4, 512, 13000, True),
+    (64, 25, 8, 1, 408, 5000, True),        # 400 blocks: cut at head_dim 64 (98 against 126 us) ...
+    (128, 25, 8, 1, 408, 5000, False),      # ... and not at 128
+    (64, 20, 8, 1, 37, 350, False),         # short blocks: the merge costs more
+])
+def test_prefill_split_rule(d, B, H, gqa, C, hist, pays):
+    """The session's choice between whole blocks and the key-split launch: two of eight KV heads keep all of the history,
+    the others an eighth (profiles/prefill_split_rule.md has the shapes that it is fitted to)."""
+    from paper_2606_06302_amd.runner import split_pays
+    keep = np.where(np.arange(H) % 4 == 0, hist, hist // 8)
+    assert split_pays(d, C, gqa, np.broadcast_to(keep, (B, H))) == pays
