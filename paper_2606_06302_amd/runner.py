@@ -334,10 +334,13 @@ def split_pays(head_dim, chunk_len, gqa, hist) -> bool:
 
 
 class PrefillSession:
-    """Pool, chunk inputs and output of one chunked-prefill workload (one layer)."""
+    """Pool, chunk inputs and output of one chunked-prefill workload (one layer).  workspace: scratch of the key-split
+    launch (a uint8 tensor of at least tg_prefill_workspace_bytes, up to 60 MB), shared by sessions whose calls run
+    one after another on a stream, as a model's layers do; the session allocates its own where none, or too small a
+    one, is given."""
 
     def __init__(self, wl, tables: Tables = None, layer=0, fill="device", pool=None, device="cuda", schedule=True,
-                 hist_len=None):
+                 hist_len=None, workspace=None):
         from workloads import S_K, S_POOL, S_Q, S_V, device_normal_, host_pool, host_prefill_inputs, page_elems
         g = wl.geom
         assert wl.chunk_len >= 1, "prefill workloads need a chunk length"
@@ -380,8 +383,10 @@ class PrefillSession:
         # scheduled ahead of time: partials of the key-split launch where it pays
         pays = schedule and split_pays(g.head_dim, C, g.gqa, self.hist[:, layer])
         ws_bytes = tg.tg_prefill_workspace_bytes(self.args) if pays else 0
+        self.workspace = None
         if ws_bytes:
-            self.workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=device)
+            fits = workspace is not None and workspace.numel() * workspace.element_size() >= ws_bytes
+            self.workspace = workspace if fits else torch.empty(ws_bytes, dtype=torch.uint8, device=device)
             self.args.workspace, self.args.workspace_bytes = self.workspace.data_ptr(), ws_bytes
 
     def run(self, stream=None):

@@ -203,6 +203,26 @@ def test_prefill_key_split_clamps_lengths(d):
 
 
 @pytest.mark.parametrize("d", [128, 64])
+def test_prefill_layers_share_a_workspace(d):
+    """Sessions of two layers on one key-split workspace, run one after the other, give what each gives on its own;
+    a tensor that is too small is not used."""
+    _gpu()
+    g = Geometry(2, 2, 8, d, 16, 2)
+    wl = custom(656, g, 1, "bf16", 5000, chunk_len=70)
+    tables = Tables(wl)
+    alone = [PrefillSession(wl, tables=tables, layer=l) for l in range(2)]
+    assert all(s.workspace is not None for s in alone)
+    ws = torch.full((max(s.workspace.numel() for s in alone),), 0xFF, dtype=torch.uint8, device="cuda")
+    shared = [PrefillSession(wl, tables=tables, layer=l, pool=alone[l].pool, workspace=ws) for l in range(2)]
+    for s in (*alone, *shared):
+        s.run()
+    torch.cuda.synchronize()
+    for l in range(2):
+        assert shared[l].workspace is ws and torch.equal(shared[l].out, alone[l].out)
+    assert PrefillSession(wl, tables=tables, pool=alone[0].pool, workspace=ws[:-1]).workspace.numel() == ws.numel()
+
+
+@pytest.mark.parametrize("d", [128, 64])
 def test_prefill_key_split_rows_with_infinite_scores_first(d):
     """Rows whose scores overflow to -inf over the first keys, beside rows of the same wave whose scores there are
     finite and raise the running maximum: the key-split launch gives the keys of score -inf no weight."""
