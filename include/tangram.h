@@ -408,11 +408,9 @@ int32_t tg_append(const tg_append_args* args, void* hip_stream);
  *   initialisation needed; calls that share one must not overlap in time) for
  *   the key-split launch: blocks much longer than the others are cut by keys,
  *   their fp32 partials merged by a second launch on the same stream, and
- *   block_order is not used.  It pays where the longest block, in tiles, is
- *   longer than about 1.25 times the launch's tiles / 208, plus 12 (head_dim
- *   128), or 2 times the tiles / 448, plus 10 (64): few
- *   requests, or very unequal histories.  The caller decides by giving a
- *   workspace or none.  The size does not grow with the batch or the history,
+ *   block_order is not used.  It pays with few
+ *   requests or very unequal histories (tg_prefill_split_pays); the caller
+ *   decides by giving a workspace or none.  The size does not grow with the batch or the history,
  *   55 MB at head_dim 128 and 60 MB at 64 once chunk_len * gqa reaches 256;
  *   layers that run one after another can share one.  It is 0, and a workspace
  *   is not used, past 512 (request, KV head) units or 1024 blocks; one that is
@@ -462,6 +460,14 @@ enum { TG_PREFILL_ROWS = 256, TG_PREFILL_TILE = 64 };
 int32_t tg_prefill_schedule(const tg_geometry* geom, int32_t batch, int32_t chunk_len, int32_t layer,
                             const int32_t* kv_len, int32_t n_xcd, int32_t* order, int32_t capacity,
                             int32_t* num_blocks);
+
+/* 4b. Whether the key-split launch of tg_prefill (a workspace given) is
+ * expected to beat its whole-block launch with tg_prefill_schedule's order for
+ * these lengths (host): both are played through on 8 XCDs of 32 CUs.  pays out:
+ * 1 or 0; 0 where no workspace is used.  Arguments and errors as
+ * tg_prefill_schedule. */
+int32_t tg_prefill_split_pays(const tg_geometry* geom, int32_t batch, int32_t chunk_len, int32_t layer,
+                              const int32_t* kv_len, int32_t* pays);
 
 size_t  tg_prefill_workspace_bytes(const tg_prefill_args* args);
 int32_t tg_prefill(const tg_prefill_args* args, void* hip_stream);

@@ -581,69 +581,170 @@ int32_t tg_build_plan(const tg_geometry* geom, int32_t batch, int32_t layer, con
 
 // Ahead-of-time workgroup schedule of tg_prefill: LPT placement of the
 // (request, KV head) units on the XCDs, longest blocks first on each XCD.
+}  // extern "C"
+
+// Key tiles of a prefill launch's blocks, and its blocks by XCD: units placed
+// longest first, each on the least-loaded XCD, each XCD's blocks longest first.
+struct PrefillBlocks {
+  int64_t row_tiles;
+  std::vector<int64_t> hist_tiles, chunk_tiles;                  // per unit, per row tile
+  std::vector<std::vector<std::pair<int64_t, int64_t>>> on_xcd;  // (unit, row tile)
+  int64_t cost(const std::pair<int64_t, int64_t>& b) const { return hist_tiles[b.first] + chunk_tiles[b.second]; }
+  size_t longest_list() const {
+    size_t n = 0;
+    for (const auto& v : on_xcd) n = std::max(n, v.size());
+    return n;
+  }
+};
+
+static int32_t prefill_blocks(const tg_geometry* geom, int32_t batch, int32_t chunk_len, int32_t layer,
+                              const int32_t* kv_len, int32_t n_xcd, PrefillBlocks* out) {
+  if (int32_t rc = tg::check_geometry(geom)) return rc;
+  if (batch < 1 || chunk_len < 1) return fail(TG_ERR_INVALID_ARG, "batch and chunk_len must be >= 1");
+  if (layer < 0 || layer >= geom->num_layers) return fail(TG_ERR_INVALID_ARG, "layer %d out of range", layer);
+  if (n_xcd < 1 || n_xcd > 64) return fail(TG_ERR_INVALID_ARG, "n_xcd must be in 1..64");
+  const int64_t L = geom->num_layers, H = geom->num_kv_heads, gqa = geom->num_q_heads / geom->num_kv_heads;
+  const int64_t C = chunk_len, rows = C * gqa;
+  const int64_t row_tiles = tg::ceil_div(rows, TG_PREFILL_ROWS);
+  const int64_t n_units = (int64_t)batch * H;
+  if (n_units * row_tiles > INT32_MAX / 2) return fail(TG_ERR_INVALID_ARG, "too many prefill blocks");
+  // cost of every block and unit
+  out->row_tiles = row_tiles;
+  out->chunk_tiles.resize(row_tiles);
+  for (int64_t rt = 0; rt < row_tiles; ++rt) {
+    const int64_t i_last = std::min(C - 1, (std::min((rt + 1) * TG_PREFILL_ROWS, rows) - 1) / gqa);
+    out->chunk_tiles[rt] = i_last / TG_PREFILL_TILE + 1;
+  }
+  std::vector<int64_t> unit_cost(n_units);
+  out->hist_tiles.resize(n_units);
+  for (int64_t u = 0; u < n_units; ++u) {
+    const int64_t b = u / H, h = u % H;
+    const int64_t len = kv_len[(b * L + layer) * H + h];
+    if (len < 0) return fail(TG_ERR_INVALID_ARG, "negative kv_len at request %lld head %lld", (long long)b,
+                             (long long)h);
+    out->hist_tiles[u] = tg::ceil_div(len, TG_PREFILL_TILE);
+    unit_cost[u] = 0;
+    for (int64_t rt = 0; rt < row_tiles; ++rt) unit_cost[u] += out->cost({u, rt});
+  }
+  // units to XCDs, longest first, each to the least-loaded XCD (ties: lowest index)
+  std::vector<int64_t> units(n_units);
+  for (int64_t u = 0; u < n_units; ++u) units[u] = u;
+  std::stable_sort(units.begin(), units.end(), [&](int64_t a, int64_t b) { return unit_cost[a] > unit_cost[b]; });
+  std::vector<int64_t> load(n_xcd, 0);
+  out->on_xcd.assign(n_xcd, {});
+  for (int64_t u : units) {
+    int x = 0;
+    for (int k = 1; k < n_xcd; ++k)
+      if (load[k] < load[x]) x = k;
+    load[x] += unit_cost[u];
+    for (int64_t rt = 0; rt < row_tiles; ++rt) out->on_xcd[x].emplace_back(u, rt);
+  }
+  for (auto& v : out->on_xcd)
+    std::stable_sort(v.begin(), v.end(), [&](const std::pair<int64_t, int64_t>& a, const std::pair<int64_t, int64_t>& b) {
+      const int64_t ca = out->cost(a), cb = out->cost(b);
+      return ca != cb ? ca > cb : a < b;
+    });
+  return TG_OK;
+}
+
+// Time, in key tiles, until the last of these workgroups is done on one XCD:
+// dispatched in order to the first of `places` that is free, a start of two
+// tiles each.
+static int64_t finish_tiles(const std::vector<int64_t>& tiles, int places) {
+  std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> busy;
+  int64_t last = 0;
+  for (int64_t t : tiles) {
+    int64_t at = 0;
+    if ((int)busy.size() == places) {
+      at = busy.top();
+      busy.pop();
+    }
+    at += t + 2;
+    busy.push(at);
+    last = std::max(last, at);
+  }
+  return last;
+}
+
+extern "C" {
+
 int32_t tg_prefill_schedule(const tg_geometry* geom, int32_t batch, int32_t chunk_len, int32_t layer,
                             const int32_t* kv_len, int32_t n_xcd, int32_t* order, int32_t capacity,
                             int32_t* num_blocks) {
   return guarded([&]() -> int32_t {
     if (int32_t rc = tg::check_geometry(geom)) return rc;
     if (!kv_len || !num_blocks) return fail(TG_ERR_INVALID_ARG, "NULL array");
-    if (batch < 1 || chunk_len < 1) return fail(TG_ERR_INVALID_ARG, "batch and chunk_len must be >= 1");
-    if (layer < 0 || layer >= geom->num_layers) return fail(TG_ERR_INVALID_ARG, "layer %d out of range", layer);
-    if (n_xcd < 1 || n_xcd > 64) return fail(TG_ERR_INVALID_ARG, "n_xcd must be in 1..64");
-    const int64_t L = geom->num_layers, H = geom->num_kv_heads, gqa = geom->num_q_heads / geom->num_kv_heads;
-    const int64_t C = chunk_len, rows = C * gqa;
-    const int64_t row_tiles = tg::ceil_div(rows, TG_PREFILL_ROWS);
-    const int64_t n_units = (int64_t)batch * H;
-    if (n_units * row_tiles > INT32_MAX / 2) return fail(TG_ERR_INVALID_ARG, "too many prefill blocks");
-    // cost of every block and unit
-    std::vector<int64_t> chunk_tiles(row_tiles), unit_cost(n_units);
-    for (int64_t rt = 0; rt < row_tiles; ++rt) {
-      const int64_t i_last = std::min(C - 1, (std::min((rt + 1) * TG_PREFILL_ROWS, rows) - 1) / gqa);
-      chunk_tiles[rt] = i_last / TG_PREFILL_TILE + 1;
-    }
-    std::vector<int64_t> hist_tiles(n_units);
-    for (int64_t u = 0; u < n_units; ++u) {
-      const int64_t b = u / H, h = u % H;
-      const int64_t len = kv_len[(b * L + layer) * H + h];
-      if (len < 0) return fail(TG_ERR_INVALID_ARG, "negative kv_len at request %lld head %lld", (long long)b,
-                               (long long)h);
-      hist_tiles[u] = tg::ceil_div(len, TG_PREFILL_TILE);
-      unit_cost[u] = 0;
-      for (int64_t rt = 0; rt < row_tiles; ++rt) unit_cost[u] += hist_tiles[u] + chunk_tiles[rt];
-    }
-    // units to XCDs, longest first, each to the least-loaded XCD (ties: lowest index)
-    std::vector<int64_t> units(n_units);
-    for (int64_t u = 0; u < n_units; ++u) units[u] = u;
-    std::stable_sort(units.begin(), units.end(),
-                     [&](int64_t a, int64_t b) { return unit_cost[a] > unit_cost[b]; });
-    std::vector<int64_t> load(n_xcd, 0);
-    std::vector<std::vector<std::pair<int64_t, int64_t>>> blocks(n_xcd);   // (u, rt)
-    for (int64_t u : units) {
-      int x = 0;
-      for (int k = 1; k < n_xcd; ++k)
-        if (load[k] < load[x]) x = k;
-      load[x] += unit_cost[u];
-      for (int64_t rt = 0; rt < row_tiles; ++rt) blocks[x].emplace_back(u, rt);
-    }
-    size_t longest = 0;
-    for (auto& v : blocks) {
-      std::stable_sort(v.begin(), v.end(), [&](const std::pair<int64_t, int64_t>& a, const std::pair<int64_t, int64_t>& b) {
-        const int64_t ca = hist_tiles[a.first] + chunk_tiles[a.second];
-        const int64_t cb = hist_tiles[b.first] + chunk_tiles[b.second];
-        if (ca != cb) return ca > cb;
-        return a < b;
-      });
-      longest = std::max(longest, v.size());
-    }
-    const int64_t total = (int64_t)n_xcd * (int64_t)longest;
+    PrefillBlocks p;
+    if (int32_t rc = prefill_blocks(geom, batch, chunk_len, layer, kv_len, n_xcd, &p)) return rc;
+    const int64_t total = (int64_t)n_xcd * (int64_t)p.longest_list();
     *num_blocks = (int32_t)total;
     if (!order) return TG_OK;   // size query
     if (capacity < total) return fail(TG_ERR_BUFFER_TOO_SMALL, "order holds %d, need %lld", capacity, (long long)total);
     for (int64_t k = 0; k < total; ++k) {
-      const auto& v = blocks[k % n_xcd];
+      const auto& v = p.on_xcd[k % n_xcd];
       const size_t j = (size_t)(k / n_xcd);
-      order[k] = j < v.size() ? (int32_t)(v[j].first * row_tiles + v[j].second) : -1;
+      order[k] = j < v.size() ? (int32_t)(v[j].first * p.row_tiles + v[j].second) : -1;
     }
+    return TG_OK;
+  });
+}
+
+// Both launches are played through in key tiles, XCD by XCD.  A line on the
+// longest block and the launch's total, which this replaces, did not see that
+// the row tiles of a piece run on one XCD: 19 groups of 17 workgroups, three of
+// them on one XCD's 32 CUs, took 445 us where the 238 whole blocks took 382.
+int32_t tg_prefill_split_pays(const tg_geometry* geom, int32_t batch, int32_t chunk_len, int32_t layer,
+                              const int32_t* kv_len, int32_t* pays) {
+  return guarded([&]() -> int32_t {
+    if (int32_t rc = tg::check_geometry(geom)) return rc;
+    if (!kv_len || !pays) return fail(TG_ERR_INVALID_ARG, "NULL array");
+    constexpr int kXcds = 8, kCus = 32;   // CUs of an XCD
+    PrefillBlocks p;
+    if (int32_t rc = prefill_blocks(geom, batch, chunk_len, layer, kv_len, kXcds, &p)) return rc;
+    *pays = 0;
+    const int64_t n_units = (int64_t)p.hist_tiles.size(), rt = p.row_tiles;
+    const int d = geom->head_dim;
+    if ((d != 64 && d != 128) || n_units > tg::kPrefillSplitMaxUnits || n_units * rt > tg::kPrefillSplitMaxBlocks)
+      return TG_OK;
+    // whole blocks
+    const bool pairs = d == 64 && kXcds * p.longest_list() > (size_t)tg::kPrefillOnePerCuBlocks;
+    int64_t whole = 0;
+    for (const auto& v : p.on_xcd) {
+      std::vector<int64_t> tiles;
+      for (const auto& b : v) tiles.push_back(p.cost(b));
+      whole = std::max(whole, finish_tiles(tiles, pairs ? 2 * kCus : kCus));
+    }
+    // the cut the kernel makes: cut units first, then the others by falling length
+    std::vector<int64_t> full(n_units);
+    int64_t total = 0;
+    for (int64_t u = 0; u < n_units; ++u) total += full[u] = p.hist_tiles[u] + p.chunk_tiles[rt - 1];
+    const int64_t T = std::max<int64_t>(tg::kPrefillSplitMinTiles, tg::ceil_div(total * rt, tg::prefill_split_target(d)));
+    std::vector<std::pair<int64_t, int64_t>> groups;   // (unit, piece)
+    for (int c = 0; c < 8; ++c)
+      for (int64_t u = 0; u < n_units; ++u) {
+        const int64_t pieces = tg::ceil_div(full[u], T);
+        if ((pieces > 1 ? 0 : 7 - full[u] * 6 / T) != c) continue;
+        for (int64_t k = 0; k < pieces; ++k) groups.emplace_back(u, k);
+      }
+    std::vector<std::vector<int64_t>> tiles(kXcds);
+    int64_t partials = 0;
+    for (size_t g = 0; g < groups.size(); ++g)
+      for (int64_t r = 0; r < rt; ++r) {
+        const int64_t n = p.cost({groups[g].first, r}), k = tg::ceil_div(n, T), i = groups[g].second;
+        if (i >= k) continue;
+        partials += k > 1;
+        tiles[g % kXcds].push_back((i + 1) * n / k - i * n / k);
+      }
+    int64_t split = 0;
+    for (const auto& v : tiles) split = std::max(split, finish_tiles(v, d == 128 ? kCus : 2 * kCus));
+    // a tile takes longer with every CU busy, and the merge reads the partials
+    // back.  Fitted to 523 shapes timed both ways: at 128 the slower launch is
+    // chosen at a loss of 1.5 % at most where it is the cut one, at 64 in 2 of
+    // 264 shapes over 3 % (12 % at most)
+    const double block = (double)std::min<int64_t>((int64_t)chunk_len * (geom->num_q_heads / geom->num_kv_heads),
+                                                   TG_PREFILL_ROWS) / TG_PREFILL_ROWS;
+    const double cost = (d == 128 ? 1.3 * (double)split + 2.0 : 1.45 * (double)split + 3.0) + 0.03 * (double)partials * block;
+    *pays = (double)whole >= cost;
     return TG_OK;
   });
 }

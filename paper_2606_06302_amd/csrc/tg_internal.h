@@ -28,4 +28,21 @@ inline bool aligned16(std::initializer_list<const void*> ptrs) {
   return true;
 }
 
+// The cut of the key-split prefill launch, made on the device and foreseen by
+// tg_prefill_split_pays: pieces of at least kPrefillSplitMinTiles key tiles,
+// about prefill_split_target() of them, for at most so many units and blocks.
+constexpr int kPrefillSplitMinTiles = 3;
+constexpr int kPrefillSplitMaxUnits = 512;    // one thread of a workgroup per unit
+constexpr int kPrefillSplitMaxBlocks = 1024;  // past it blocks outnumber the CUs by far and even out by themselves
+// A little under the workgroups that run at once (one per CU at head_dim 128,
+// two at 64), because cutting into equal pieces rounds up.  One request, chunk
+// 512, 16384 tokens, with 160 / 208 / 256 / 320: 94 / 81 / 110 / 99 us at 128.
+// At 64, chunk 512, with 352 / 448 / 512: one request over 16384 tokens 60 / 56
+// / 65 us, two over 8192 61 / 57 / 68, four 95 / 109 / 110; over 57 shapes 0.99
+// / 1 / 1.02.
+constexpr int prefill_split_target(int head_dim) { return head_dim == 128 ? 208 : 448; }
+// Whole-block launches of head_dim 64 with more blocks than this run two
+// workgroups per CU.
+constexpr int kPrefillOnePerCuBlocks = 512;
+
 }  // namespace tg

@@ -140,17 +140,11 @@ struct PrefillParams {
 // us; four requests, chunk 512 over 8192 166 -> 117 us; head_dim 64, five
 // requests, chunk 333, 74 -> 45 us.  Where no block is much longer than the
 // mean per CU the merge costs more than the cut saves (four requests, chunk
-// 512 over 2048 tokens: 61 against 72 us): the caller gives no workspace there.
-constexpr int kSplitMinTiles = 3;
-constexpr int kSplitMaxUnits = kBlock;   // one thread per unit
-constexpr int kSplitMaxBlocks = 1024;    // past it blocks outnumber the CUs by far and even out by themselves
-// Pieces to aim at: a little under the workgroups that run at once (one per CU
-// at head_dim 128, two at 64), because cutting into equal pieces rounds up.
-// One request, chunk 512, 16384 tokens, with 160 / 208 / 256 / 320: 94 / 81 /
-// 110 / 99 us at 128.  At 64, chunk 512, with 352 / 448 / 512: one request over
-// 16384 tokens 60 / 56 / 65 us, two over 8192 61 / 57 / 68, four 95 / 109 / 110;
-// over 57 shapes 0.99 / 1 / 1.02.
-constexpr int split_target(int d) { return d == 128 ? 208 : 448; }
+// 512 over 2048 tokens: 61 against 72 us): the caller gives no workspace there
+// (tg_prefill_split_pays).
+constexpr int kSplitMinTiles = tg::kPrefillSplitMinTiles;
+static_assert(tg::kPrefillSplitMaxUnits == kBlock, "one thread per unit");
+constexpr int split_target(int d) { return tg::prefill_split_target(d); }
 // a cut unit of n tiles has at most n / T + 1 <= 2n / T pieces
 constexpr int split_slots(int d) { return 2 * split_target(d); }
 
@@ -641,7 +635,7 @@ SplitLayout split_layout(const tg_geometry& g, int batch, int chunk_len) {
   const int64_t rows = (int64_t)chunk_len * (g.num_q_heads / g.num_kv_heads);
   const int64_t row_tiles = (rows + kRows - 1) / kRows;
   const int64_t units = (int64_t)batch * g.num_kv_heads;
-  if (units > kSplitMaxUnits || units * row_tiles > kSplitMaxBlocks) return s;
+  if (units > tg::kPrefillSplitMaxUnits || units * row_tiles > tg::kPrefillSplitMaxBlocks) return s;
   s.row_tiles = (int)row_tiles;
   s.part_waves = (int)((rows < kRows ? rows : kRows) + 31) / 32;
   s.groups = split_target(g.head_dim) / s.row_tiles + (int)units;   // sum over units of ceil(n / T)
@@ -736,7 +730,7 @@ int32_t tg_prefill(const tg_prefill_args* a, void* hip_stream) {
   // out better over the CUs one at a time, the longest first (512 blocks of 8
   // requests 63 us against 65, 336 of 14 37 against 38): LDS that is not used
   // keeps the second workgroup off.
-  const size_t one_per_cu = g.head_dim == 64 && blocks <= 512 ? 24 << 10 : 0;
+  const size_t one_per_cu = g.head_dim == 64 && blocks <= tg::kPrefillOnePerCuBlocks ? 24 << 10 : 0;
   auto kernel = g.head_dim == 128 ? tg_prefill_kernel<128, false, 2> : tg_prefill_kernel<64, false, 2>;
   hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), one_per_cu, st, p);
   hipError_t e = hipGetLastError();

@@ -317,22 +317,6 @@ class DecodeSession:
 REALTIME_HZ = 100e6
 
 
-def split_pays(head_dim, chunk_len, gqa, hist) -> bool:
-    """Whether cutting the longest prefill blocks by keys beats launching whole blocks, for one layer's retained
-    history lengths hist ([B][H], or flat): the longest block's key tiles bound the whole-block launch, the even
-    share of the pieces it aims at (208 at head_dim 128, 448 at 64) the key-split one, which adds a merge that grows
-    with the rows of a block.  Whole blocks of head_dim 64 share a CU in pairs and even out better, so their share
-    weighs more.  The lines are fitted to 523 shapes measured both ways, 1 to 48 requests, chunks of 16 to 4096 over
-    200 to 16384 tokens.  Where they choose the slower launch: at 128, cut 4 of 259 shapes at a loss of 3 to 10 %; at
-    64, 4 of 264 at 4 to 12 %; the others lose a gain (at 128 up to 1.74 times, in a launch of a few very long
-    blocks; at 64 up to 1.09)."""
-    rows, last = chunk_len * gqa, (chunk_len - 1) // 64 + 1          # 256 query rows per block, 64 keys per tile
-    tiles = -(-np.asarray(hist, dtype=np.int64) // 64) + last        # of every unit's last row tile
-    total, block = float(tiles.sum()) * -(-rows // 256), min(rows, 256) / 256
-    line = 1.25 * total / 208 + 3 + 9 * block if head_dim == 128 else 2 * total / 448 + 5 + 5 * block
-    return float(tiles.max()) >= line
-
-
 class PrefillSession:
     """Pool, chunk inputs and output of one chunked-prefill workload (one layer).  workspace: scratch of the key-split
     launch (a uint8 tensor of at least tg_prefill_workspace_bytes, up to 60 MB), shared by sessions whose calls run
@@ -381,7 +365,7 @@ class PrefillSession:
                                          self.pool, self.t.d_pt_pages, self.d_offsets, self.d_kv_len,
                                          self.d_group_of, self.d_slot_of, self.out, block_order=self.d_order)
         # scheduled ahead of time: partials of the key-split launch where it pays
-        pays = schedule and split_pays(g.head_dim, C, g.gqa, self.hist[:, layer])
+        pays = schedule and tg.tg_prefill_split_pays(g, B, C, layer, self.hist)
         ws_bytes = tg.tg_prefill_workspace_bytes(self.args) if pays else 0
         self.workspace = None
         if ws_bytes:

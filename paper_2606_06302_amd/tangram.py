@@ -123,6 +123,7 @@ _SIGS = {
     "tg_prefill_workspace_bytes": (_sz, [C.POINTER(tg_prefill_args)]),
     "tg_prefill": (_i32, [C.POINTER(tg_prefill_args), _P]),
     "tg_prefill_schedule": (_i32, [_G, _i32, _i32, _i32, _P, _i32, _P, _i32, _P]),
+    "tg_prefill_split_pays": (_i32, [_G, _i32, _i32, _i32, _P, _P]),
     "tg_compress_plan": (_i32, [_G, _i32, _i32, _i32, _P, _P, _P, _P, _P, _P, _P, _P, _i32, _P, _i32, _P, _P, _P]),
     "tg_compress": (_i32, [C.POINTER(tg_compress_args), _P]),
     "tg_memory_footprint": (_i32, [_G, _i32, _P, _P, _P, _P, C.POINTER(tg_footprint)]),
@@ -329,6 +330,14 @@ def tg_prefill_schedule(geom, batch, chunk_len, layer, kv_len, n_xcd=8):
     order = np.zeros(max(1, n.value), np.int32)
     _check(_lib.tg_prefill_schedule(*head, _ptr(order), len(order), C.byref(n)), "tg_prefill_schedule")
     return order[: n.value]
+
+
+def tg_prefill_split_pays(geom, batch, chunk_len, layer, kv_len) -> bool:
+    g = _geom(geom)
+    n = C.c_int32(0)
+    _check(_lib.tg_prefill_split_pays(C.byref(g), int(batch), int(chunk_len), int(layer), _ptr(_host(kv_len, np.int32)),
+                                      C.byref(n)), "tg_prefill_split_pays")
+    return bool(n.value)
 
 
 def tg_prefill_workspace_bytes(args: tg_prefill_args) -> int:

@@ -687,13 +687,29 @@ def test_bins_per_decode_workgroup_refuses():
     (128, 1, 8, 4, 512, 13000, True),       # one request, a long history
     (128, 16, 8, 4, 512, 4000, False),      # blocks enough, of one length
     (64, 1, 8, 4, 512, 13000, True),
-    (64, 25, 8, 1, 408, 5000, True),        # 400 blocks: cut at head_dim 64 (98 against 126 us) ...
-    (128, 25, 8, 1, 408, 5000, False),      # ... and not at 128
+    (64, 25, 8, 1, 408, 5000, True),        # 400 blocks one per CU, two rounds of them: cut at head_dim 64
     (64, 20, 8, 1, 37, 350, False),         # short blocks: the merge costs more
+    (128, 7, 2, 16, 266, 13000, False),     # 17 row tiles a piece: three pieces on one XCD's 32 CUs
+    (128, 7, 2, 16, 120, 13000, True),      # 8 row tiles: they fit
+    (96, 1, 8, 4, 512, 13000, False),       # no such kernel
 ])
-def test_prefill_split_rule(d, B, H, gqa, C, hist, pays):
-    """The session's choice between whole blocks and the key-split launch: two of eight KV heads keep all of the history,
-    the others an eighth (profiles/prefill_split_rule.md has the shapes that it is fitted to)."""
-    from paper_2606_06302_amd.runner import split_pays
+def test_prefill_split_pays(d, B, H, gqa, C, hist, pays):
+    """The choice between whole blocks and the key-split launch: a quarter of the KV heads keep all of the history, the
+    others an eighth."""
     keep = np.where(np.arange(H) % 4 == 0, hist, hist // 8)
-    assert split_pays(d, C, gqa, np.broadcast_to(keep, (B, H))) == pays
+    kv = np.ascontiguousarray(np.broadcast_to(keep, (B, 1, H))).astype(np.int32)
+    assert tg.tg_prefill_split_pays(Geometry(1, H, H * gqa, d, 16, 1), B, C, 0, kv) == pays
+
+
+def test_prefill_split_pays_up_to_512_units():
+    kv = np.full((65, 1, 8), 300, np.int32)
+    kv[0, 0, 0] = 9000
+    g = Geometry(1, 8, 8, 128, 16, 1)
+    assert tg.tg_prefill_split_pays(g, 64, 5, 0, kv[:64]) and not tg.tg_prefill_split_pays(g, 65, 5, 0, kv)
+
+
+def test_prefill_split_pays_refuses():
+    g, kv = Geometry(1, 2, 4, 128, 16, 1), np.full((1, 1, 2), 100, np.int32)
+    for args in ((g, 0, 8, 0, kv), (g, 1, 0, 0, kv), (g, 1, 8, 1, kv), (g, 1, 8, 0, -kv)):
+        with pytest.raises(tg.TangramError):
+            tg.tg_prefill_split_pays(*args)
