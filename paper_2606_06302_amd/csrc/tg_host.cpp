@@ -611,9 +611,10 @@ static int32_t prefill_blocks(const tg_geometry* geom, int32_t batch, int32_t ch
   // cost of every block and unit
   out->row_tiles = row_tiles;
   out->chunk_tiles.resize(row_tiles);
+  int64_t all_chunk_tiles = 0;
   for (int64_t rt = 0; rt < row_tiles; ++rt) {
     const int64_t i_last = std::min(C - 1, (std::min((rt + 1) * TG_PREFILL_ROWS, rows) - 1) / gqa);
-    out->chunk_tiles[rt] = i_last / TG_PREFILL_TILE + 1;
+    all_chunk_tiles += out->chunk_tiles[rt] = i_last / TG_PREFILL_TILE + 1;
   }
   std::vector<int64_t> unit_cost(n_units);
   out->hist_tiles.resize(n_units);
@@ -623,8 +624,7 @@ static int32_t prefill_blocks(const tg_geometry* geom, int32_t batch, int32_t ch
     if (len < 0) return fail(TG_ERR_INVALID_ARG, "negative kv_len at request %lld head %lld", (long long)b,
                              (long long)h);
     out->hist_tiles[u] = tg::ceil_div(len, TG_PREFILL_TILE);
-    unit_cost[u] = 0;
-    for (int64_t rt = 0; rt < row_tiles; ++rt) unit_cost[u] += out->cost({u, rt});
+    unit_cost[u] = out->hist_tiles[u] * row_tiles + all_chunk_tiles;
   }
   // units to XCDs, longest first, each to the least-loaded XCD (ties: lowest index)
   std::vector<int64_t> units(n_units);
@@ -708,12 +708,28 @@ int32_t tg_prefill_split_pays(const tg_geometry* geom, int32_t batch, int32_t ch
       return TG_OK;
     // whole blocks
     const bool pairs = d == 64 && kXcds * p.longest_list() > (size_t)tg::kPrefillOnePerCuBlocks;
-    int64_t whole = 0;
+    int64_t whole = 0, all_tiles = 0;
+    std::vector<int64_t> xcd_tiles;
     for (const auto& v : p.on_xcd) {
-      std::vector<int64_t> tiles;
-      for (const auto& b : v) tiles.push_back(p.cost(b));
-      whole = std::max(whole, finish_tiles(tiles, pairs ? 2 * kCus : kCus));
+      xcd_tiles.clear();
+      for (const auto& b : v) {
+        xcd_tiles.push_back(p.cost(b));
+        all_tiles += xcd_tiles.back();
+      }
+      whole = std::max(whole, finish_tiles(xcd_tiles, pairs ? 2 * kCus : kCus));
     }
+    // a tile takes longer with every CU busy, and the merge reads the partials
+    // back.  Fitted to 523 shapes timed both ways: at 128 the slower launch is
+    // chosen at a loss of 1.5 % at most where it is the cut one, at 64 in 2 of
+    // 264 shapes over 3 % (12 % at most)
+    const double block = (double)std::min<int64_t>((int64_t)chunk_len * (geom->num_q_heads / geom->num_kv_heads),
+                                                   TG_PREFILL_ROWS) / TG_PREFILL_ROWS;
+    const int places = d == 128 ? kCus : 2 * kCus;
+    auto better = [&](int64_t split, int64_t partials) {
+      const double cost = (d == 128 ? 1.3 * (double)split + 2.0 : 1.45 * (double)split + 3.0) + 0.03 * (double)partials * block;
+      return (double)whole >= cost;
+    };
+    if (!better(all_tiles / (kXcds * places), 0)) return TG_OK;   // not even evenly spread and without a merge
     // the cut the kernel makes: cut units first, then the others by falling length
     std::vector<int64_t> full(n_units);
     int64_t total = 0;
@@ -736,15 +752,8 @@ int32_t tg_prefill_split_pays(const tg_geometry* geom, int32_t batch, int32_t ch
         tiles[g % kXcds].push_back((i + 1) * n / k - i * n / k);
       }
     int64_t split = 0;
-    for (const auto& v : tiles) split = std::max(split, finish_tiles(v, d == 128 ? kCus : 2 * kCus));
-    // a tile takes longer with every CU busy, and the merge reads the partials
-    // back.  Fitted to 523 shapes timed both ways: at 128 the slower launch is
-    // chosen at a loss of 1.5 % at most where it is the cut one, at 64 in 2 of
-    // 264 shapes over 3 % (12 % at most)
-    const double block = (double)std::min<int64_t>((int64_t)chunk_len * (geom->num_q_heads / geom->num_kv_heads),
-                                                   TG_PREFILL_ROWS) / TG_PREFILL_ROWS;
-    const double cost = (d == 128 ? 1.3 * (double)split + 2.0 : 1.45 * (double)split + 3.0) + 0.03 * (double)partials * block;
-    *pays = (double)whole >= cost;
+    for (const auto& v : tiles) split = std::max(split, finish_tiles(v, places));
+    *pays = better(split, partials);
     return TG_OK;
   });
 }

@@ -326,9 +326,12 @@ def tg_prefill_schedule(geom, batch, chunk_len, layer, kv_len, n_xcd=8):
     kv = _host(kv_len, np.int32)
     n = C.c_int32(0)
     head = (C.byref(g), int(batch), int(chunk_len), int(layer), _ptr(kv), int(n_xcd))
-    _check(_lib.tg_prefill_schedule(*head, None, 0, C.byref(n)), "tg_prefill_schedule")
-    order = np.zeros(max(1, n.value), np.int32)
-    _check(_lib.tg_prefill_schedule(*head, _ptr(order), len(order), C.byref(n)), "tg_prefill_schedule")
+    order = np.zeros(4096, np.int32)       # one call for all but the largest launches
+    rc = _lib.tg_prefill_schedule(*head, _ptr(order), len(order), C.byref(n))
+    if rc == TG_ERR_BUFFER_TOO_SMALL:
+        order = np.zeros(n.value, np.int32)
+        rc = _lib.tg_prefill_schedule(*head, _ptr(order), len(order), C.byref(n))
+    _check(rc, "tg_prefill_schedule")
     return order[: n.value]
 
 

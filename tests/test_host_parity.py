@@ -273,6 +273,14 @@ def test_prefill_schedule_random_bit_exact(data):
     assert got.tolist() == ref.tolist()
 
 
+def test_prefill_schedule_of_many_blocks():
+    """More blocks than the binding's first call has room for."""
+    kv = np.random.default_rng(3).integers(0, 5000, (40, 1, 8)).astype(np.int32)
+    got = tg.tg_prefill_schedule(Geometry(1, 8, 128, 64, 16, 2), 40, 300, 0, kv)
+    ref, _ = oracle.prefill_schedule(kv, 0, 300, 16, 8)
+    assert len(got) > 4096 and np.array_equal(got, ref)
+
+
 def test_prefill_schedule_errors():
     geom = Geometry(1, 2, 4, 128, 16, 1)
     kv = np.ones((1, 1, 2), np.int32)
