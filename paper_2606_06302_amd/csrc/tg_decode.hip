@@ -431,7 +431,7 @@ __global__ void __launch_bounds__(kBlock) tg_decode_kernel(DecodeParams p, const
 // Bound by HBM.  At head_dim 64 a page holds half the bytes for the same
 // softmax; two pages per step keep the wave's instructions per byte near those
 // at 128.  32 requests, gqa 4, 2048 to 16384 tokens (182 and 88 MB a layer): 33
-// and 19 us, 5.5 and 4.7 TB/s, against 42 and 26 us on the vector kernel.
+// and 20 us, 5.6 and 4.4 TB/s, against 42 and 26 us on the vector kernel.
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
