@@ -1416,7 +1416,9 @@ constexpr int kMaxGqa = 16;
 //     show on the host.
 //   bf16 head_dim 64, gqa 1: 64 requests of 200 to 1000 tokens 13.1 against 14.0
 //     (19 against 19), 32 of 300 to 3000 11.6 against 15.0 (17 against 20);
-//     396 MB 81 against 70.
+//     396 MB 81 against 70.  With few requests level, but for one very long
+//     context, whose more pieces the merge pays for (40000 tokens, 8 KV heads
+//     14.5 against 13.1, 2 heads 19.4 against 14.4).
 // Plans of few bins (one worker per unit, say) are bound by one worker, and
 // four waves on a bin win at up to four heads: 128 bins of one unit each (16
 // requests, 8192 tokens), bf16 head_dim 64, gqa 4 133 against 204 us, gqa 8 (64
